@@ -192,7 +192,9 @@ int rsst_steps_out(rsst_handle h, void* const* U_list, void* const* U1_list, int
  * the CFL maximum and the next dt of every step inside it, U written once at
  * the end; the stage buffer's contents are then unspecified); there, with a
  * CFL step and t_end > 0, the steps left once t reaches t_end (dt = 0, which
- * leave U unchanged) are skipped. */
+ * leave U unchanged) are skipped.  A 2D grid may run its steps in pairs, each
+ * step one launch, through the stage buffer (whose contents are then
+ * unspecified too). */
 int rsst_steps(rsst_handle h, void* U, int nsteps, double dt_fixed, void* stream);
 
 /* Returns the time t and the dt the next CFL step will use (Sec. 4.1, the

@@ -29,7 +29,8 @@ struct rsst_solver {
   size_t elem;       // bytes per stored value
   void* u1;          // stage buffer, owned
   double* scal;      // device scalars, owned
-  double* blkmax;    // per-workgroup maxima of c_tot of the current state, owned
+  double* blkmax;    // per-workgroup maxima of c_tot of the current state, owned; 2D: then as many for
+                     // the state after an odd number of one-launch steps within a call
   double* part;      // diag partials, owned
   double* diag_out;  // 8 doubles, owned
   int npart;
@@ -107,7 +108,7 @@ static int validate(const rsst_config* c) {
 // state, scalar and maxima pointers are left for the caller to set.
 static void fill_args(const rsst_config* cfg, long long ncell, StageArgs& a) {
   std::memset(&a, 0, sizeof(a));
-  a.geo = rsstk::plan_geometry(cfg->ndim, cfg->n);
+  a.geo = rsstk::plan_geometry(cfg->ndim, cfg->n, cfg->bc_lo[0] == RSST_PERIODIC);
   a.ncell = ncell;
   for (int d = 0; d < 3; ++d) {
     a.bc_lo[d] = cfg->bc_lo[d];
@@ -144,9 +145,16 @@ static void fill_args(const rsst_config* cfg, long long ncell, StageArgs& a) {
   a.bg_axis = cfg->prec == RSST_FP32_PERT ? cfg->bg_axis : -1;
   a.nbg = (a.bg_axis >= 0) ? cfg->n[a.bg_axis] : 1;
   a.bg_uniform = (a.bg_axis == -1 || (cfg->ndim >= 2 && a.bg_axis == cfg->ndim - 1)) ? 1 : 0;
-  a.nblk = a.geo.ntile_s * a.geo.nchunk;
+  a.nslot = a.geo.nslot;
   a.big = (cfg->ndim == 3 && (long long)(cfg->ndim + 2) * ncell *
                                  (long long)(cfg->prec == RSST_FP32_PERT ? 4 : 8) >= (1ll << 31)) ? 1 : 0;
+}
+
+// The scalars and maxima of a solver (or of the fixed scratch).
+static void use_scalars(StageArgs& a, double* scal, double* blkmax) {
+  a.scal = scal;
+  a.t_in = a.t_out = scal + rsstk::kTime;
+  a.blkmax = a.blkmax_out = blkmax;
 }
 
 // ---- rsst_step_noalloc: one step with no allocation ------------------------
@@ -226,9 +234,10 @@ int rsst_init(const rsst_config* cfg, void* stream, rsst_handle* out) {
   const size_t ubytes = (size_t)h->nv * h->ncell * h->elem;
   if (hipMalloc(&h->u1, ubytes) != hipSuccess) { delete h; return RSST_E_NOMEM; }
   const size_t nscal = rsstk::kNumScalars;
+  const size_t nmax = (size_t)a.nslot * (cfg->ndim == 2 ? 2 : 1);
   h->scal = h->blkmax = h->part = h->diag_out = nullptr;
   if (hipMalloc((void**)&h->scal, nscal * sizeof(double)) != hipSuccess ||
-      hipMalloc((void**)&h->blkmax, (size_t)a.nblk * sizeof(double)) != hipSuccess ||
+      hipMalloc((void**)&h->blkmax, nmax * sizeof(double)) != hipSuccess ||
       hipMalloc((void**)&h->part, (size_t)h->npart * 8 * sizeof(double)) != hipSuccess ||
       hipMalloc((void**)&h->diag_out, 8 * sizeof(double)) != hipSuccess) {
     (void)hipFree(h->u1); (void)hipFree(h->scal); (void)hipFree(h->blkmax); (void)hipFree(h->part);
@@ -249,14 +258,13 @@ int rsst_init(const rsst_config* cfg, void* stream, rsst_handle* out) {
   const size_t adj_z = h->adj_work ? rsstk::adjoint_zeroed_offset(cfg->ndim, cfg->n, h->ncell) : 0;
   const size_t adj_n = h->adj_work ? rsstk::adjoint_workspace_doubles(cfg->ndim, cfg->n, h->ncell) : 0;
   if (hipMemsetAsync(h->scal, 0, nscal * sizeof(double), s) != hipSuccess ||
-      hipMemsetAsync(h->blkmax, 0, (size_t)a.nblk * sizeof(double), s) != hipSuccess ||
+      hipMemsetAsync(h->blkmax, 0, nmax * sizeof(double), s) != hipSuccess ||
       (adj_n > adj_z && hipMemsetAsync(h->adj_work + adj_z, 0, (adj_n - adj_z) * sizeof(double), s) != hipSuccess) ||
       hipStreamSynchronize(s) != hipSuccess) {
     rsst_destroy(h);
     return RSST_E_DEVICE;
   }
-  a.scal = h->scal;
-  a.blkmax = h->blkmax;
+  use_scalars(a, h->scal, h->blkmax);
   h->primed = false;
   *out = h;
   return RSST_OK;
@@ -301,26 +309,65 @@ int rsst_step(rsst_handle h, void* U, double dt_fixed, void* stream) {
   return rsst_stage(h, U, 2, dt_fixed, stream);
 }
 
-int rsst_step_out(rsst_handle h, const void* U, void* U1, void* Unext, double dt_fixed, void* stream) {
-  if (!h || !U || !U1 || !Unext || !std::isfinite(dt_fixed)) return RSST_E_ARG;
-  if (U1 == U || Unext == U || U1 == Unext) return RSST_E_ARG;
-  hipStream_t s = (hipStream_t)stream;
-  StageArgs a = h->args;
-  a.dt_fixed = dt_fixed > 0.0 ? dt_fixed : 0.0;
+// Sets the maxima of U and t for a first CFL step.
+static int prime_once(rsst_handle h, const void* U, double dt_fixed, hipStream_t s) {
   if (dt_fixed <= 0.0 && !h->primed) {
     if (rsstk::launch_prime(h->args, U, 0.0, 0, s) != hipSuccess) return RSST_E_DEVICE;
     h->primed = true;
   }
-  // the two stages of rsst_step with the caller's buffers in place of the
-  // stage buffer and of U
+  return RSST_OK;
+}
+
+// A 2D step in one launch, from uin to uout (another array), U1 to u1out
+// unless null.  A CFL step reads the maxima and t in every workgroup, so it
+// leaves the new ones in the other buffers: such steps come in pairs, half 0
+// and half 1, after which they are back in their own.
+static hipError_t step2d(rsst_handle h, int half, const void* uin, void* u1out, void* uout, double dt_fixed,
+                         hipStream_t s) {
+  StageArgs a = h->args;
+  a.dt_fixed = dt_fixed > 0.0 ? dt_fixed : 0.0;
+  a.uin = a.un = uin;
+  a.u1out = u1out;
+  a.uout = uout;
+  if (!(dt_fixed > 0.0)) {
+    double* const blk[2] = {h->blkmax, h->blkmax + a.nslot};
+    double* const t[2] = {h->scal + rsstk::kTime, h->scal + rsstk::kTimeAlt};
+    a.blkmax = blk[half];
+    a.blkmax_out = blk[1 - half];
+    a.t_in = t[half];
+    a.t_out = t[1 - half];
+  }
+  return h->elem == sizeof(float) ? rsstk::launch_step2d<float>(a, s) : rsstk::launch_step2d<double>(a, s);
+}
+
+// The two stages of rsst_step, one launch each, with the caller's buffers in
+// place of the stage buffer and (Unext) of U.
+static hipError_t step_split(rsst_handle h, const void* U, void* U1, void* Unext, double dt_fixed, hipStream_t s) {
+  StageArgs a = h->args;
+  a.dt_fixed = dt_fixed > 0.0 ? dt_fixed : 0.0;
   a.uin = U;
   a.un = nullptr;
   a.uout = U1;
-  if (rsstk::launch_stage(a, 1, s) != hipSuccess) return RSST_E_DEVICE;
+  const hipError_t e = rsstk::launch_stage(a, 1, s);
+  if (e != hipSuccess) return e;
   a.uin = U1;
   a.un = U;
   a.uout = Unext;
-  if (rsstk::launch_stage(a, 2, s) != hipSuccess) return RSST_E_DEVICE;
+  return rsstk::launch_stage(a, 2, s);
+}
+
+static bool distinct(const void* a, const void* b, const void* c) { return a != b && a != c && b != c; }
+
+int rsst_step_out(rsst_handle h, const void* U, void* U1, void* Unext, double dt_fixed, void* stream) {
+  if (!h || !U || !U1 || !Unext || !std::isfinite(dt_fixed)) return RSST_E_ARG;
+  if (!distinct(U, U1, Unext)) return RSST_E_ARG;
+  hipStream_t s = (hipStream_t)stream;
+  int st = prime_once(h, U, dt_fixed, s);
+  if (st != RSST_OK) return st;
+  // in one launch where that leaves the maxima and t in place
+  const hipError_t e = h->args.geo.fused && dt_fixed > 0.0 ? step2d(h, 0, U, U1, Unext, dt_fixed, s)
+                                                           : step_split(h, U, U1, Unext, dt_fixed, s);
+  if (e != hipSuccess) return RSST_E_DEVICE;
   h->primed = true;
   return RSST_OK;
 }
@@ -331,7 +378,21 @@ int rsst_steps_out(rsst_handle h, void* const* U_list, void* const* U1_list, int
   for (int n = 0; n < nsteps; ++n)
     if (!U_list[n] || !U1_list[n] || !U_list[n + 1]) return RSST_E_ARG;
   for (int n = 0; n < nsteps; ++n) {
-    const int st = rsst_step_out(h, U_list[n], U1_list[n], U_list[n + 1], dt_fixed, stream);
+    void* const* u = U_list + n;
+    if (h->args.geo.fused && !(dt_fixed > 0.0) && n + 1 < nsteps && distinct(u[0], U1_list[n], u[1]) &&
+        distinct(u[1], U1_list[n + 1], u[2])) {
+      // a pair of CFL steps, one launch each
+      hipStream_t s = (hipStream_t)stream;
+      const int st = prime_once(h, u[0], dt_fixed, s);
+      if (st != RSST_OK) return st;
+      if (step2d(h, 0, u[0], U1_list[n], u[1], dt_fixed, s) != hipSuccess ||
+          step2d(h, 1, u[1], U1_list[n + 1], u[2], dt_fixed, s) != hipSuccess)
+        return RSST_E_DEVICE;
+      h->primed = true;
+      ++n;
+      continue;
+    }
+    const int st = rsst_step_out(h, u[0], U1_list[n], u[1], dt_fixed, stream);
     if (st != RSST_OK) return st;
   }
   return RSST_OK;
@@ -360,7 +421,19 @@ int rsst_steps(rsst_handle h, void* U, int nsteps, double dt_fixed, void* stream
     h->primed = true;
     return RSST_OK;
   }
-  for (int q = 0; q < nsteps; ++q) {
+  int q = 0;
+  if (h && U && std::isfinite(dt_fixed) && nsteps > 1 && h->args.geo.fused) {
+    // pairs of steps, one launch each: from U to the stage buffer and back
+    hipStream_t s = (hipStream_t)stream;
+    const int st = prime_once(h, U, dt_fixed, s);
+    if (st != RSST_OK) return st;
+    for (; q + 1 < nsteps; q += 2)
+      if (step2d(h, 0, U, nullptr, h->u1, dt_fixed, s) != hipSuccess ||
+          step2d(h, 1, h->u1, nullptr, U, dt_fixed, s) != hipSuccess)
+        return RSST_E_DEVICE;
+    h->primed = true;
+  }
+  for (; q < nsteps; ++q) {
     int st = rsst_step(h, U, dt_fixed, stream);
     if (st != RSST_OK) return st;
   }
@@ -500,7 +573,7 @@ int rsst_step_noalloc(const rsst_config* cfg, void* U, double dt_fixed, uint32_t
   fill_args(cfg, ncell, a);
   // scratch layout: scalars | CFL maxima | U1, each 256-byte aligned
   const size_t o_blk = round256(rsstk::kNumScalars * sizeof(double));
-  const size_t o_u1 = o_blk + round256((size_t)a.nblk * sizeof(double));
+  const size_t o_u1 = o_blk + round256((size_t)a.nslot * sizeof(double));
   const size_t need = o_u1 + (size_t)(cfg->ndim + 2) * (size_t)ncell * elem;
   if (need > kScratchBytes) return RSST_E_SCRATCH;
   int dev = 0;
@@ -509,8 +582,7 @@ int rsst_step_noalloc(const rsst_config* cfg, void* U, double dt_fixed, uint32_t
   st = scratch_on(dev, &base);
   if (st != RSST_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  a.scal = (double*)base;
-  a.blkmax = (double*)(base + o_blk);
+  use_scalars(a, (double*)base, (double*)(base + o_blk));
   void* u1 = base + o_u1;
   a.dt_fixed = dt_fixed > 0.0 ? dt_fixed : 0.0;
   hipLaunchKernelGGL(noalloc_clear_kernel, dim3(1), dim3(64), 0, s, a.scal);

@@ -2,13 +2,13 @@
 // background, advanced by one persistent kernel per run, captured in a HIP
 // graph and replayed.
 //
-// Work items are (stage q, box b, strip block p), q = 2 n + stage - 1 for
-// step n.  A strip block is `groups` consecutive strips of `strip` rows
-// (y, the marched axis) processed side by side by one 256-thread workgroup
-// (a box row of nwx <= 4 waves; narrow boxes run 4/nwx strips at once).
-// Tickets are handed out in q-major order by one atomic counter, and an item
-// only waits on items with smaller tickets:
-//   * the strip blocks of its box at q-1 that hold a row within two cells
+// Work items are (stage q, box b, row block p), q = 2 n + stage - 1 for
+// step n.  A row block is `rows` rows (y, the marched axis) of a box, a
+// quarter of them marched by each wave of a 256-thread workgroup.  The boxes
+// are dealt to queues; tickets of a queue are handed out in q-major order by
+// one atomic counter, and an item only waits on items of its own box, which
+// hold smaller tickets of the same queue:
+//   * the row blocks of its box at q-1 that hold a row within two cells
 //     of its own rows (through the boundary rule: a periodic y wraps the
 //     first block onto the last ones), or whose rows are within two cells
 //     of its own; this orders every read of a row by the previous stage
@@ -18,6 +18,22 @@
 //     box, whose per-box maximum of c_tot gives the box's CFL dt.
 // Every waiting item holds a ticket larger than the ones it waits for, and
 // those were taken by running workgroups, so the queue cannot deadlock.
+//
+// Queues and XCDs.  Data written by one XCD of the MI355X is seen by another
+// only after the writer's whole L2 was written back and the reader's
+// invalidated.  With one queue for the chip every item did both, several
+// times, and these set the pace: 512 FP32 boxes of 64..256 cells a side ran
+// 20 steps in 62.8 ms with 16-row strips (4.6 Gcell-updates/s).  So there
+// are eight queues, and a queue is worked on by the workgroups of one XCD
+// only (the first whose workgroup comes to it; the hardware register XCC_ID
+// tells a workgroup its XCD): every wait is between CUs that share an L2,
+// which a store reaches before it is counted complete and which agent-scope
+// loads read past the CU's own cache.  The same run then takes 14.1 ms (20.5
+// Gcell-updates/s; 32-row strips 13.3 ms, against 21.7 ms for the best strips
+// before), bound by FP64 issue: 0.8 of the rate at which a SIMD can issue the
+// ~390 instructions of a row (rsst_stage2.h).  Where the boxes are too few or too
+// uneven to keep eight queues level, one queue serves the chip, with one
+// write-back per item and one invalidation per wait.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -37,17 +53,18 @@ namespace rsstk {
 constexpr int kBatchThreads = 256;  // one box row: at most 4 waves
 // Persistent workgroups per CU.  A workgroup is one wave per SIMD, so this is
 // also the waves per SIMD the kernel is compiled for (its register budget).
-// Measured with 137-VGPR one-plane strips, three per CU were 0-65% slower
-// than two on every strip choice (more items in flight, each slower).
-constexpr int kBatchPerCU = 2;
+// 512 FP32 boxes, 20 steps, 16-row strips: 14.4 ms with three, 15.8 ms with
+// four (128 VGPRs, which spill).
+constexpr int kBatchPerCU = 3;
+constexpr int kXcds = 8;            // XCDs of an MI355X, each with its own L2
+constexpr int kLdAgent = 16;        // load cache policy sc1: agent scope, past the CU's cache
 
 struct BoxDev {
   StageArgs s1, s2;  // stage views of the box (pointers into U_all / U1_all)
   double cfl_h;      // cfl * h of the box
   int nblk;          // strip blocks
   int rbase;         // index of the box's first item in a stage
-  int groups;        // strips per block
-  int pad;
+  int rows;          // rows of a block
 };
 
 // A work item: strip block `blk` of box `box`, and the blocks of the same
@@ -61,20 +78,31 @@ struct Item {
 };
 
 struct BatchState {
-  unsigned* ticket;              // next ticket
+  unsigned* ticket;              // [kXcds] next ticket of each queue
+  int* owner;                    // [kXcds] XCD working on each queue, -1 none yet
   unsigned long long* maxbits;   // [nbox][max_steps + 1] max c_tot of the input of each step
   unsigned* cnt2;                // [nbox][max_steps] stage-2 blocks done per step
   unsigned* done;                // [2 max_steps][nitem] item done flags
   double* tacc;                  // [nbox] time reached
   unsigned* flags;               // non-physical flags
   int nbox, nitem, nsteps, max_steps;
-  unsigned total;                // 2 nsteps nitem tickets
+  int local;                     // one queue per XCD (else queue 0 serves the chip)
+  int qbase[kXcds + 1];          // first item of each queue (its items are consecutive)
   unsigned long long wait_ticks; // longest dependency wait, in wall-clock ticks (100 MHz)
 };
 
-__device__ __forceinline__ unsigned ld_acquire(const unsigned* p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+template <typename T>
+__device__ __forceinline__ T ld_agent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// The XCD this wave runs on.
+__device__ __forceinline__ int xcc_id() {
+  return (int)(__builtin_amdgcn_s_getreg(20 /* HW_REG_XCC_ID */ | (0 << 6) | ((4 - 1) << 11)) & (kXcds - 1));
+}
+
+// Every store and atomic of the wave so far has reached its L2.
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Flag bit of a run whose queue gave up on a dependency wait (reported by
 // rsst_batch_poll as RSST_E_DEVICE): a wait past its deadline means a
@@ -82,20 +110,14 @@ __device__ __forceinline__ unsigned ld_acquire(const unsigned* p) {
 // is skipped (marked done, nothing stored) and every workgroup drains.
 constexpr unsigned kQueueTimeout = 8u;
 
-// Spins until *p >= v or the wall clock passes `deadline`; false on timeout.
-__device__ __forceinline__ bool wait_at_least(const unsigned* p, unsigned v, unsigned long long deadline) {
-  while (ld_acquire(p) < v) {
-    if (wall_clock64() > deadline) return false;
-    __builtin_amdgcn_s_sleep(2);
-  }
-  return true;
-}
-
 // Clears the per-run counters (graph-safe: a kernel, not a memset node).
 __global__ void __launch_bounds__(256) batch_reset_kernel(BatchState S) {
   const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long stride = (long long)gridDim.x * blockDim.x;
-  if (tid == 0) *S.ticket = 0u;
+  if (tid < kXcds) {
+    S.ticket[tid] = 0u;
+    S.owner[tid] = -1;
+  }
   for (long long q = tid; q < (long long)S.nbox * (S.max_steps + 1); q += stride) S.maxbits[q] = 0ull;
   for (long long q = tid; q < (long long)S.nbox * S.max_steps; q += stride) S.cnt2[q] = 0u;
   for (long long q = tid; q < 2ll * S.max_steps * S.nitem; q += stride) S.done[q] = 0u;
@@ -132,8 +154,9 @@ __global__ void __launch_bounds__(256) batch_prime_kernel(const BoxDev* __restri
   }
 }
 
-// Completion of an item: its per-box c_tot maximum (stage 2), the box time,
-// then the done flag and the per-step stage-2 count with release order.
+// Completion of an item, by thread 0 after every wave's stores are complete:
+// its per-box c_tot maximum (stage 2), the box time, then the done flag and
+// the per-step stage-2 count.
 struct Pending {
   int b, p, n;
   unsigned q, r;
@@ -145,86 +168,161 @@ __device__ __forceinline__ void signal_done(const BatchState& S, const Pending& 
   if (d.st2) {
     double m = 0.0;
     for (int w = 0; w < kBatchThreads / 64; ++w) m = fmax(m, red[w]);
-    atomicMax(S.maxbits + (long long)d.b * (S.max_steps + 1) + d.n + 1,
-              (unsigned long long)__double_as_longlong(m));
-    if (d.p == 0) S.tacc[d.b] += d.dt;
-    __threadfence();
+    __hip_atomic_fetch_max(S.maxbits + (long long)d.b * (S.max_steps + 1) + d.n + 1,
+                           (unsigned long long)__double_as_longlong(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (d.p == 0)
+      __hip_atomic_store(S.tacc + d.b, ld_agent(S.tacc + d.b) + d.dt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __hip_atomic_store(S.done + (long long)d.q * S.nitem + d.r, 1u, __ATOMIC_RELEASE,
-                     __HIP_MEMORY_SCOPE_AGENT);
+  wait_stores();
+  if (!S.local) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __hip_atomic_store(S.done + (long long)d.q * S.nitem + d.r, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (d.st2)
-    __hip_atomic_fetch_add(S.cnt2 + (long long)d.b * S.max_steps + d.n, 1u, __ATOMIC_RELEASE,
+    __hip_atomic_fetch_add(S.cnt2 + (long long)d.b * S.max_steps + d.n, 1u, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Thread 0 acts for the workgroup in exactly one region per iteration
-// besides the dependency wait: it signals the item just finished and takes
-// the next ticket.  Both sit between barriers, so no single-thread region
-// ends one iteration and another begins the next; the compiler could
-// otherwise join the two across the back edge into a loop that thread 0
-// leaves while the rest of its wave goes round without it.
+// The next ticket for a workgroup working on queue cur (of XCD x): the queue
+// and the ticket, or ticket ~0 when no queue is left for this XCD.  tried:
+// queues looked at so far, starting with the XCD's own.
+__device__ __forceinline__ unsigned take_ticket(const BatchState& S, int x, int& tried, int& cur) {
+  for (;;) {
+    if (cur >= 0) {
+      const unsigned total = 2u * (unsigned)S.nsteps * (unsigned)(S.qbase[cur + 1] - S.qbase[cur]);
+      const unsigned t = __hip_atomic_fetch_add(S.ticket + cur, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (t < total) return t;
+      cur = -1;
+      if (!S.local) return ~0u;
+    }
+    if (tried == kXcds) return ~0u;
+    const int q = S.local ? (x + tried) & (kXcds - 1) : 0;
+    ++tried;
+    if (S.local) {
+      int o = -1;
+      const bool mine = __hip_atomic_compare_exchange_strong(S.owner + q, &o, x, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT);
+      if (mine || o == x) cur = q;
+    } else {
+      cur = q;
+    }
+  }
+}
+
+// One stage of an item's rows: each of the four waves takes a quarter of them
+// and marches it strip by strip across the row, so any row width keeps all
+// four busy and no barrier falls inside the item.
+template <int STAGE, typename ST, int FORM>
+__device__ __forceinline__ double item_rows(const StageArgs& A, double* lds, int r0, int rows, double dt,
+                                            unsigned& bad) {
+  const Geometry& G = A.geo;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r1 = min(r0 + rows, G.nm);
+  const int per = (r1 - r0 + kWaves2 - 1) / kWaves2;
+  const int k0 = r0 + w * per, k1 = min(k0 + per, r1);
+  double cmax = 0.0;
+  if (k0 < k1) {
+    const Tile2 none{nullptr, 0, 0};
+    for (int c = 0; c < G.cols.ncol; ++c)
+      cmax = fmax(cmax, march2<kSplit, STAGE, ST, FORM, kLdAgent>(A, lane_of(G.cols, G.nx, A.bc_lo[0] == 0, c),
+                                                                  lds + w * kLds2, none, k0, k1, k0, k1, true,
+                                                                  [&]() { return dt; }, bad));
+  }
+  return cmax;
+}
+
+// Thread 0 acts for the workgroup in exactly one region per iteration: it
+// signals the item just finished and takes the next ticket.  Both sit
+// between barriers, so no single-thread region ends one iteration and another
+// begins the next; the compiler could otherwise join the two across the back
+// edge into a loop that thread 0 leaves while the rest of its wave goes round
+// without it.  The dependency wait is the whole first wave's, one lane per
+// flag, in a loop that is uniform over the wave.
 template <typename ST, int FORM>
-__global__ void __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(kBatchPerCU))) batch_kernel(const BoxDev* __restrict__ boxes,
-                                                            const Item* __restrict__ items,
-                                                            BatchState S) {
+__global__ void __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(kBatchPerCU))) batch_kernel(
+    const BoxDev* __restrict__ boxes, const Item* __restrict__ items, BatchState S) {
   extern __shared__ double lds[];
   __shared__ unsigned tshare, skip;
+  __shared__ int qshare, tried;  // queue worked on, queues looked at so far
+  __shared__ Pending prev;       // the item being worked on
   __shared__ double red[kBatchThreads / 64];
-  const int tid = threadIdx.x;
-  Pending prev{-1, 0, 0, 0u, 0u, false, 0.0};
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int x = xcc_id();
+  if (tid == 0) {
+    qshare = -1;
+    tried = 0;
+    prev.b = -1;
+  }
+  __syncthreads();
   for (;;) {
     if (tid == 0) {
       if (prev.b >= 0) signal_done(S, prev, red);
-      tshare = atomicAdd(S.ticket, 1u);
+      tshare = take_ticket(S, x, tried, qshare);
     }
     __syncthreads();
     const unsigned t = __builtin_amdgcn_readfirstlane(tshare);  // uniform: SGPR box fields
+    const int qu = __builtin_amdgcn_readfirstlane(qshare);
     __syncthreads();
-    if (t >= S.total) break;
-    const int q = (int)(t / (unsigned)S.nitem), r = (int)(t % (unsigned)S.nitem);
-    const Item it = items[r];
+    if (t == ~0u) break;
+    const int i0 = S.qbase[qu], ni = S.qbase[qu + 1] - i0;
+    const int q = (int)(t / (unsigned)ni), r = i0 + (int)(t % (unsigned)ni);
     // box and block are workgroup-uniform: said explicitly, every field of
     // the box's stage views stays in scalar registers (otherwise the compiler
     // wraps each buffer access built from them in a per-lane waterfall loop)
-    const int b = __builtin_amdgcn_readfirstlane(it.box), p = __builtin_amdgcn_readfirstlane(it.blk), n = q >> 1;
+    const int b = __builtin_amdgcn_readfirstlane(items[r].box), p = __builtin_amdgcn_readfirstlane(items[r].blk);
+    const int n = q >> 1;
     const bool st2 = (q & 1) != 0;
     const BoxDev& B = boxes[b];
-    if (tid == 0) {
+    if (w == 0) {
+      // lane d < ndep: neighbour block d of the previous stage; the next
+      // lane: for stage 1, the box's stage-2 count of the previous step
+      const int ndep = q > 0 ? items[r].ndep : 0;
+      const unsigned* p0 = nullptr;
+      unsigned need = 1u;
+      if (lane < ndep) {
+        p0 = S.done + (long long)(q - 1) * S.nitem + B.rbase + items[r].dep[lane];
+      } else if (lane == ndep && !st2 && n > 0) {
+        p0 = S.cnt2 + (long long)b * S.max_steps + (n - 1);
+        need = (unsigned)B.nblk;
+      }
       const unsigned long long deadline = wall_clock64() + S.wait_ticks;
       bool ok = true;
-      if (!st2 && n > 0)
-        ok = wait_at_least(S.cnt2 + (long long)b * S.max_steps + (n - 1), (unsigned)B.nblk, deadline);
-      if (q > 0) {
-        const unsigned* dq = S.done + (long long)(q - 1) * S.nitem + B.rbase;
-        for (int d = 0; d < it.ndep && ok; ++d) ok = wait_at_least(dq + it.dep[d], 1u, deadline);
+      for (;;) {
+        const bool here = !p0 || ld_agent(p0) >= need;
+        if (__all(here)) break;
+        if (wall_clock64() > deadline) {
+          ok = false;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(2);
       }
-      if (!ok) atomicOr(S.flags, kQueueTimeout);
-      skip = ok ? 0u : 1u;
+      if (!S.local) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      if (lane == 0) {
+        if (!ok) atomicOr(S.flags, kQueueTimeout);
+        skip = ok ? 0u : 1u;
+      }
     }
     __syncthreads();
     const bool skip_item = __builtin_amdgcn_readfirstlane(skip) != 0u;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    const unsigned long long mb = __hip_atomic_load(S.maxbits + (long long)b * (S.max_steps + 1) + n,
-                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long mb = ld_agent(S.maxbits + (long long)b * (S.max_steps + 1) + n);
     const double dt = B.cfl_h / __longlong_as_double((long long)mb);
     unsigned bad = 0;
     double cmax = 0.0;
     if (skip_item) {
       // nothing computed or stored; the item is still signalled done below
     } else if (!st2) {
-      cmax = stage_body2<1, ST, FORM, 2>(B.s1, lds, p * B.groups, dt, bad);
+      cmax = item_rows<1, ST, FORM>(B.s1, lds, p * B.rows, B.rows, dt, bad);
     } else {
-      cmax = stage_body2<2, ST, FORM, 2>(B.s2, lds, p * B.groups, dt, bad);
+      cmax = item_rows<2, ST, FORM>(B.s2, lds, p * B.rows, B.rows, dt, bad);
     }
     if (bad) atomicOr(S.flags, bad);
     if (st2) {
       const double wm = wave_max(cmax);
-      if ((tid & 63) == 0) red[tid >> 6] = wm;
+      if (lane == 0) red[w] = wm;
     }
-    // every thread's stores are complete device-wide before the signal
-    __threadfence();
+    // every wave's stores have reached L2 before the signal
+    wait_stores();
+    if (tid == 0) prev = Pending{b, p, n, (unsigned)q, (unsigned)r, st2, dt};
     __syncthreads();
-    prev = Pending{b, p, n, (unsigned)q, (unsigned)r, st2, dt};
   }
 }
 
@@ -254,6 +352,8 @@ struct rsst_batch_s {
   std::vector<BoxDev> boxes;
   std::vector<Item> items;
   int nitem;
+  int local;                      // one queue per XCD
+  int qbase[kXcds + 1];           // first item of each queue
   size_t lds_bytes;
   // device memory
   void* u1;
@@ -261,6 +361,7 @@ struct rsst_batch_s {
   Item* d_items;
   int d_items_cap;
   unsigned* d_ticket;
+  int* d_owner;
   unsigned long long* d_maxbits;
   unsigned* d_cnt2;
   unsigned* d_done;
@@ -348,12 +449,55 @@ static int plan_box(const rsst_config& c, const int strip[4], int b, std::vector
   return RSST_OK;
 }
 
-// Stage views, strip blocks and the item table for the current strip rows.
+// Deals the boxes to the queues: order lists them queue by queue (in the
+// caller's order within a queue), qfirst[q] is where queue q starts.  Each
+// box goes to the queue with the least work so far, largest box first (work:
+// wave-rows, rows times strips).  Returns 1 for a queue per XCD.  Where the
+// fullest queue holds more than 1.25 of the mean (few boxes, or a few large
+// ones), all go to queue 0 for the whole chip and 0 is returned: the chip then
+// waits for one XCD longer than the write-backs between XCDs would cost.
+static int deal_boxes(const std::vector<rsst_config>& cfg, std::vector<int>& order, int qfirst[kXcds + 1]) {
+  const int nbox = (int)cfg.size();
+  std::vector<long long> work(nbox);
+  long long sum = 0;
+  for (int b = 0; b < nbox; ++b) {
+    work[b] = (long long)plan_cols2(cfg[b].n[0], cfg[b].bc_lo[0] == RSST_PERIODIC, 2).ncol * cfg[b].n[1];
+    sum += work[b];
+  }
+  std::vector<int> by(nbox);
+  for (int b = 0; b < nbox; ++b) by[b] = b;
+  std::stable_sort(by.begin(), by.end(), [&](int p, int q) { return work[p] > work[q]; });
+  long long load[kXcds] = {0};
+  std::vector<int> queue(nbox, 0);
+  for (int b : by) {
+    const int q = (int)(std::min_element(load, load + kXcds) - load);
+    queue[b] = q;
+    load[q] += work[b];
+  }
+  const long long top = *std::max_element(load, load + kXcds);
+  const int local = top * kXcds * 4 <= sum * 5;
+  order.clear();
+  for (int q = 0; q < kXcds; ++q) {
+    qfirst[q] = (int)order.size();
+    for (int b = 0; b < nbox; ++b)
+      if ((local ? queue[b] : 0) == q) order.push_back(b);
+  }
+  qfirst[kXcds] = nbox;
+  return local;
+}
+
+// Stage views, row blocks and the item table for the current strip rows.
 static int batch_build(rsst_batch_s* h, void* U) {
   h->boxes.assign(h->nbox, BoxDev{});
   h->items.clear();
   size_t lds = 0;
-  for (int b = 0; b < h->nbox; ++b) {
+  std::vector<int> order;
+  int qfirst[kXcds + 1];
+  h->local = deal_boxes(h->cfg, order, qfirst);
+  int qu = 0;
+  for (int o = 0; o < h->nbox; ++o) {
+    const int b = order[o];
+    while (qu < kXcds && qfirst[qu] <= o) h->qbase[qu++] = (int)h->items.size();
     const rsst_config& c = h->cfg[b];
     BoxDev& B = h->boxes[b];
     B.rbase = (int)h->items.size();
@@ -368,13 +512,13 @@ static int batch_build(rsst_batch_s* h, void* U) {
     G.ns = 1;
     G.nm = c.n[1];
     G.nwx = (G.nx + 63) / 64;
-    G.ts = groups;
+    G.ts = 1;
     G.km = km;
-    G.np = 2;
+    G.cols = plan_cols2(G.nx, c.bc_lo[0] == RSST_PERIODIC, 2);
     G.ntile_s = 1;
     G.nchunk = (G.nm + G.km - 1) / G.km;
     G.threads = kBatchThreads;
-    G.lds_bytes = (size_t)carve2(groups, G.nwx, 2).total * sizeof(double);
+    G.lds_bytes = (size_t)kRed2 * sizeof(double);
     if (G.lds_bytes > lds) lds = G.lds_bytes;
     a.ncell = (long long)G.nx * G.nm;
     for (int d = 0; d < 3; ++d) {
@@ -409,10 +553,11 @@ static int batch_build(rsst_batch_s* h, void* U) {
     if (c.dt_rule == 1) hl = std::fmin(c.dx[0], c.dx[1]);
     else hl = 1.0 / (1.0 / c.dx[0] + 1.0 / c.dx[1]);
     B.cfl_h = c.cfl * hl;
-    B.groups = groups;
+    B.rows = groups * km;
     B.nblk = nblk;
   }
   h->nitem = (int)h->items.size();
+  while (qu <= kXcds) h->qbase[qu++] = h->nitem;
   h->lds_bytes = lds;
   return RSST_OK;
 }
@@ -421,6 +566,7 @@ template <typename ST>
 static hipError_t batch_launch_all(rsst_batch_s* h, hipStream_t s, int nsteps) {
   BatchState S;
   S.ticket = h->d_ticket;
+  S.owner = h->d_owner;
   S.maxbits = h->d_maxbits;
   S.cnt2 = h->d_cnt2;
   S.done = h->d_done;
@@ -430,7 +576,8 @@ static hipError_t batch_launch_all(rsst_batch_s* h, hipStream_t s, int nsteps) {
   S.nitem = h->nitem;
   S.nsteps = nsteps;
   S.max_steps = h->max_steps;
-  S.total = (unsigned)(2ll * nsteps * h->nitem);
+  S.local = h->local;
+  for (int q = 0; q <= kXcds; ++q) S.qbase[q] = h->qbase[q];
   S.wait_ticks = h->wait_ticks;
   hipLaunchKernelGGL(batch_reset_kernel, dim3(256), dim3(256), 0, s, S);
   const int bpb = 8;
@@ -523,7 +670,8 @@ int rsst_batch_init(const rsst_config* boxes, int nbox, const int64_t* offsets, 
   bool ok = hipMalloc(&h->u1, (size_t)h->total_elems * es) == hipSuccess;
   ok = ok && hipMalloc((void**)&h->d_boxes, sizeof(BoxDev) * nbox) == hipSuccess;
   ok = ok && hipMalloc((void**)&h->d_items, sizeof(Item) * (size_t)cap_items) == hipSuccess;
-  ok = ok && hipMalloc((void**)&h->d_ticket, sizeof(unsigned)) == hipSuccess;
+  ok = ok && hipMalloc((void**)&h->d_ticket, sizeof(unsigned) * kXcds) == hipSuccess;
+  ok = ok && hipMalloc((void**)&h->d_owner, sizeof(int) * kXcds) == hipSuccess;
   ok = ok && hipMalloc((void**)&h->d_maxbits, sizeof(unsigned long long) * (size_t)nbox * (max_steps + 1)) == hipSuccess;
   ok = ok && hipMalloc((void**)&h->d_cnt2, sizeof(unsigned) * (size_t)nbox * max_steps) == hipSuccess;
   ok = ok && hipMalloc((void**)&h->d_done, sizeof(unsigned) * (size_t)h->d_done_cap) == hipSuccess;
@@ -651,6 +799,7 @@ int rsst_batch_destroy(rsst_batch h) {
   (void)hipFree(h->d_boxes);
   (void)hipFree(h->d_items);
   (void)hipFree(h->d_ticket);
+  (void)hipFree(h->d_owner);
   (void)hipFree(h->d_maxbits);
   (void)hipFree(h->d_cnt2);
   (void)hipFree(h->d_done);

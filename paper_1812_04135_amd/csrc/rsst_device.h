@@ -303,10 +303,27 @@ __device__ __forceinline__ double from_right(double x) {
   return __hiloint2double(hi, lo);
 }
 
+// x in lanes whose DPP source lane is outside the moved range, else the source
+// lane's value.
+template <int CTRL>
+__device__ __forceinline__ double dpp_or_own(double x) {
+  const int lo = __double2loint(x), hi = __double2hiint(x);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
+}
+
+// Maximum over the wave, in every lane: rows of 16 lanes by row shifts, then
+// lane 15 of each row and lane 31 broadcast onward, so lane 63 holds it (six
+// steps in registers; the LDS crossbar would take ~120 cycles for each).
 __device__ __forceinline__ double wave_max(double x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
-  return x;
+  x = fmax(x, dpp_or_own<0x111>(x));  // row_shr:1
+  x = fmax(x, dpp_or_own<0x112>(x));  // row_shr:2
+  x = fmax(x, dpp_or_own<0x114>(x));  // row_shr:4
+  x = fmax(x, dpp_or_own<0x118>(x));  // row_shr:8
+  x = fmax(x, dpp_or_own<0x142>(x));  // row_bcast:15
+  x = fmax(x, dpp_or_own<0x143>(x));  // row_bcast:31
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                          __builtin_amdgcn_readlane(__double2loint(x), 63));
 }
 
 // Butterfly sum over the wave: every lane ends with the same value, formed

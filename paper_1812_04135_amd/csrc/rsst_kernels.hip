@@ -11,13 +11,16 @@
 // correction (eq. pvs_dt, App. A) and gravity (App. B).
 //
 // Work decomposition (x = axis 0, contiguous in memory):
-//   * lanes run along x: a workgroup holds whole rows of nx cells spread
-//     over nwx = ceil(nx/64) waves, so x needs no halo;
-//   * 2D and 3D: x neighbours and x plus-face states go through LDS rows
-//     with a ghost slot at each end (periodic wrap or mirror); every x flux
-//     is formed once, by the cell right of the face, and reaches the cell on
-//     its left by DPP within a wave and through one LDS seam value per wave
-//     edge after a third barrier (rsst_stage2.h, rsst_stage3.h).  1D keeps
+//   * lanes run along x.  1D and 3D: a workgroup holds whole rows of nx cells
+//     spread over nwx = ceil(nx/64) waves, so x needs no halo.  2D: each wave
+//     takes a strip of a row by itself, with halo lanes (rsst_stage2.h), and
+//     a run of steps on a grid of few tiles takes both stages in one launch;
+//     some single-stage launches hold whole rows (rsst_row2.h);
+//   * whole rows in 2D and 3D: x neighbours and x plus-face states go through
+//     LDS rows with a ghost slot at each end (periodic wrap or mirror); every
+//     x flux is formed once, by the cell right of the face, and reaches the
+//     cell on its left by DPP within a wave and through one LDS seam value per
+//     wave edge after a third barrier (rsst_row2.h, rsst_stage3.h).  1D keeps
 //     its row in one workgroup with DPP neighbours and LDS seams, the
 //     wave-edge fluxes formed by both waves (rsst_stage1.h);
 //   * 3D: each thread owns two adjacent y rows of its column, and a tile of
@@ -29,14 +32,14 @@
 //     global memory a plane ahead;
 //   * the last axis (z in 3D, y in 2D) is marched: each thread keeps its
 //     column's planes in registers, so every z face is computed once and
-//     carried to the next plane; large 2D grids march two planes per
-//     iteration;
+//     carried to the next plane;
 //   * every face state (U +- sigma/2, its pressure, c_tot and normal
 //     velocity) is computed once, by the cell that owns it;
 //   * workgroup ids are remapped so that consecutive tiles (which share
 //     halo rows) run on the same XCD and share its L2.
 #include <cstdlib>
 
+#include "rsst_row2.h"
 #include "rsst_stage1.h"
 #include "rsst_stage2.h"
 #include "rsst_stage3.h"
@@ -87,8 +90,8 @@ __global__ void __launch_bounds__(256) prime_kernel(const StageArgs A, const ST*
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = wm;
   __syncthreads();
   if (threadIdx.x == 0) {
-    A.blkmax[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-    if (set_t && blockIdx.x == 0) A.scal[kTime] = t0;
+    A.blkmax_out[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    if (set_t && blockIdx.x == 0) *A.t_out = t0;
   }
 }
 
@@ -186,59 +189,108 @@ __global__ void __launch_bounds__(kDiagThreads) diag_final_kernel(const double* 
 
 // ---------------------------------------------------------------- host side
 
-Geometry plan_geometry(int ndim, const int n[3]) {
+// Rows (2D) or planes (3D) per march of the planned grid, unless the
+// environment variable RSST_KM, read when a solver is made, sets it: the
+// results do not depend on it, which a GPU test checks for several lengths.
+static int chunk_override(int km) {
+  if (const char* e = getenv("RSST_KM")) {
+    const int v = atoi(e);
+    if (v >= 1 && v <= 4096) return v;
+  }
+  return km;
+}
+
+Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
   Geometry G{};
   G.ndim = ndim;
-  G.np = 1;
   G.nx = n[0];
   G.ns = (ndim == 3) ? n[1] : 1;
   G.nm = (ndim == 3) ? n[2] : (ndim == 2 ? n[1] : 1);
   G.nwx = (G.nx + 63) / 64;
+  G.ts = 1;
+  G.km = 1;
+  if (ndim == 2) {
+    // One stage per launch.  A chunk of km rows costs a wave about km + 1/2
+    // rows (it re-reads four and forms one extra face to start), a row 1.05
+    // us on a SIMD of its own and 0.8 us where waves share one (1024 SIMDs),
+    // and the slowest SIMD decides: the cheapest km.  Measured against the
+    // best of 16 lengths: 22.3 us per step (km 5) at 512^2, best 22.3; 54.2
+    // (10) at 1024^2, best 54.2; 133 (10) at 1000 x 3000, best 131
+    G.cols = plan_cols2(G.nx, x_per, 2);
+    int km = 1;
+    double best = 1e300;
+    for (int q = 1; q <= 64 && q <= G.nm; ++q) {
+      const long long w = ((long long)G.cols.ncol * ((G.nm + q - 1) / q) + 1023) / 1024;
+      const double c = (w == 1 ? 1.05 : 0.8 * (double)w) * (q + 0.5);
+      if (c < best) { best = c; km = q; }
+    }
+    // Whole rows instead (a workgroup of nwx waves holds a row, three barriers
+    // per row) where strips would need more waves and the grid has at most
+    // four waves per SIMD: the step is then mostly latency, and the strips'
+    // extra waves sit on some SIMDs only (us per step: 256^2 12.6, with strips
+    // 14.1; 512^2 21.2 and 23.1; but 1024^2 62 and 50, 389 x 301 25 and 17.6).
+    // Two rows per iteration where that still gives every SIMD two waves.
+    G.rows = G.cols.ncol > G.nwx && (long long)G.nwx * G.nm <= 4096 && G.nwx <= 8;
+    if (G.rows) {
+      G.np = (long long)((G.nm + 1) / 2) * G.nwx >= 2048 ? 2 : 1;
+      km = 64;
+      while (km > G.np && (G.nm + km - 1) / km < 512) km >>= 1;
+    }
+    km = chunk_override(km);
+    G.km = km < G.nm ? km : G.nm;
+    G.ntile_s = 1;
+    G.nchunk = (G.nm + G.km - 1) / G.km;
+    if (G.rows) {
+      G.nblk = G.nchunk;
+      G.threads = 64 * G.nwx;
+      G.lds_bytes = (size_t)carve2(1, G.nwx, G.np).total * sizeof(double);
+    } else {
+      G.nblk = (G.cols.ncol * G.nchunk + kWaves2 - 1) / kWaves2;
+      G.threads = 64 * kWaves2;
+      G.lds_bytes = (size_t)(kRed2 + kWaves2) * sizeof(double);
+    }
+    G.colsF = plan_cols2(G.nx, x_per, 4);
+    // Both stages in one launch: tiles of 4 r rows, one per CU (256) at a
+    // time, each 4.4 us and 0.85 us per row of its SIMDs (r + 1 rows of stage
+    // 1, r of stage 2): the smallest r that needs one round.  It saves a
+    // launch, the stage's start-up and the way of U1 through memory, and
+    // repeats the halo: with one tile per CU it is the faster one (us per
+    // step, against one stage per launch: 64^2 8.5 and 9.7, 389 x 301 14.1 and
+    // 16.5, 512^2 19.5 and 20.0, 700 x 500 21.3 and 24.1), with more the tiles'
+    // start-ups come one after the other (1024^2: 56 and 50)
+    G.colsF = plan_cols2(G.nx, x_per, 4);
+    G.rF = 1;
+    while (G.rF < kMaxRF && (long long)G.colsF.ncol * ((G.nm + 4 * G.rF - 1) / (4 * G.rF)) > 256) ++G.rF;
+    G.fused = (long long)G.colsF.ncol * ((G.nm + 4 * G.rF - 1) / (4 * G.rF)) <= 256;
+    if (const int r = chunk_override(0)) G.rF = r < kMaxRF ? r : kMaxRF;
+    G.nblkF = G.colsF.ncol * ((G.nm + 4 * G.rF - 1) / (4 * G.rF));
+    G.nslot = G.nblk > G.nblkF ? G.nblk : G.nblkF;
+    return G;
+  }
   if (ndim == 3) {
     // 3D rows of 5-8 waves run as rows of 8 (the waves past the row's end
     // compute on clamped cells and store nothing)
     if (G.nwx > 4) G.nwx = 8;
     // an even number of rows (two per thread), at most the grid's (>= 4)
     G.ts = tile_rows3(G.nwx) < (G.ns & ~1) ? tile_rows3(G.nwx) : (G.ns & ~1);
-  } else {
-    G.ts = 1;
   }
   G.ntile_s = (G.ns + G.ts - 1) / G.ts;
-  if (ndim == 1) {
-    G.km = 1;
-  } else {
-    // chunks of 1 to 128 planes (3D; 2D: 64), halved while the grid has
-    // fewer workgroups than the 256 CUs (3D: one workgroup fills a CU) or
-    // than two per CU (2D rows of fewer waves).  A plane costs a workgroup
+  if (ndim == 3) {
+    // chunks of 1 to 128 planes, halved while the grid has fewer workgroups
+    // than the 256 CUs (one workgroup fills a CU).  A plane costs a workgroup
     // about a microsecond and a half however few cells it holds (a wave runs
     // ~1000 dependent instructions per plane), so a small grid is fastest as
     // many short marches, although each chunk re-reads 4 planes and forms one
-    // extra face to start.  The environment variable RSST_KM, read when a
-    // solver is made, sets the chunk length instead: the results do not
-    // depend on it, which a GPU test checks for several lengths
-    const long long want = ndim == 3 ? 256 : 512;
-    int km = ndim == 3 ? 128 : 64;
-    // 2D rows of up to eight waves march two planes per iteration (twice the
-    // independent work per thread and half the barriers per plane) when
-    // two-plane chunks still give every SIMD two waves (2048 waves); smaller
-    // grids run one plane per iteration, in more and shorter marches
-    // (measured: the 512^2 bubble 12.4 -> 13.0 Gcell-updates/s with two,
-    // the 256^2 adjoint forward 4.3 -> 5.4 ms per 400 steps)
-    G.np = (ndim == 2 && G.nwx <= 8 && (long long)((G.nm + 1) / 2) * G.nwx >= 2048) ? 2 : 1;
-    const int kmin = G.np;  // a march iteration takes np planes: no shorter chunk
-    while (km > kmin && (long long)G.ntile_s * ((G.nm + km - 1) / km) < want) km >>= 1;
-    if (const char* e = getenv("RSST_KM")) {
-      const int v = atoi(e);
-      if (v >= 1 && v <= 4096) km = v;
-    }
+    // extra face to start
+    int km = 128;
+    while (km > 1 && (long long)G.ntile_s * ((G.nm + km - 1) / km) < 256) km >>= 1;
+    km = chunk_override(km);
     G.km = km < G.nm ? km : G.nm;
   }
   G.nchunk = (G.nm + G.km - 1) / G.km;
+  G.nblk = G.nslot = G.ntile_s * G.nchunk;
   G.threads = 64 * G.nwx * (ndim == 3 ? G.ts / 2 : G.ts);
-  G.lds_bytes = (size_t)(ndim == 3 ? carve3(G.ts, G.nwx).total
-                                    : (ndim == 2 ? carve2(G.ts, G.nwx, G.np).total
-                                                 : carve1(G.nwx).total)) *
-                sizeof(double);
+  G.lds_bytes = (size_t)(ndim == 3 ? carve3(G.ts, G.nwx).total : carve1(G.nwx).total) * sizeof(double);
   return G;
 }
 
@@ -258,7 +310,7 @@ hipError_t launch_stage(const StageArgs& a, int stage, hipStream_t s) {
 template <typename ST>
 static hipError_t launch_prime_p(const StageArgs& a, const void* u, double t0, int set_t,
                                  hipStream_t s) {
-  const dim3 grid((unsigned)a.nblk), block(256);
+  const dim3 grid((unsigned)a.nslot), block(256);
   switch (a.geo.ndim) {
     case 1: hipLaunchKernelGGL((prime_kernel<1, ST>), grid, block, 0, s, a, (const ST*)u, t0, set_t); break;
     case 2: hipLaunchKernelGGL((prime_kernel<2, ST>), grid, block, 0, s, a, (const ST*)u, t0, set_t); break;
@@ -276,7 +328,9 @@ hipError_t launch_prime(const StageArgs& a, const void* u, double t0, int set_t,
 // and the dt formula of stage 1 over the stored maxima.
 __global__ void __launch_bounds__(256) next_dt_kernel(const StageArgs A) {
   __shared__ double red[4];
-  const double m = grid_max_from_blocks(A, red);
+  GridMax gm;
+  gm.begin(A, red);
+  const double m = gm.finish(A, red);
   if (threadIdx.x == 0) A.scal[kDtNext] = m > 0.0 ? cfl_dt_of_max(A, m) : 0.0;
 }
 

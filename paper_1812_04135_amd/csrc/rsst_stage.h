@@ -227,38 +227,59 @@ __device__ __forceinline__ Face<NV> face_from_left(const Face<NV>& s) {
 }
 
 // Tile id -> XCD: dispatch is round-robin over the 8 XCDs, so consecutive
-// tiles (which share halo rows) are remapped onto one XCD and its L2.
+// tiles (which share halo rows) are remapped onto one XCD and its L2.  XCD x
+// gets nblk / 8 consecutive tiles, one more for x < nblk % 8.
 __device__ __forceinline__ int xcd_tile(int b, int nblk) {
-  return ((nblk & 7) == 0) ? (b & 7) * (nblk >> 3) + (b >> 3) : b;
+  const int x = b & 7, per = nblk >> 3;
+  return x * per + min(x, nblk & 7) + (b >> 3);
 }
 
 // CFL step from the maxima of c_tot that the last stage 2 (or the prime
 // kernel) stored per workgroup: dt = cfl h / max, cut at t_end.  Formed by
-// every workgroup of stage 1 at its start, the same bits in each (a maximum
-// does not depend on its order).  Includes a workgroup barrier; red is not
-// written again in stage 1.
-__device__ __forceinline__ double grid_max_from_blocks(const StageArgs& A, double* red) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double m = 0.0;
-  for (int b = threadIdx.x; b < A.nblk; b += blockDim.x) m = fmax(m, A.blkmax[b]);
-  m = wave_max(m);
-  if (lane == 0) red[w] = m;
-  __syncthreads();
-  m = 0.0;
-  for (int q = 0; q < (int)(blockDim.x >> 6); ++q) m = fmax(m, red[q]);
-  return m;
-}
-
+// every workgroup of stage 1, the same bits in each (a maximum does not
+// depend on its order).
 __device__ __forceinline__ double cfl_dt_of_max(const StageArgs& A, double m) {
-  const double t = A.scal[kTime];
+  const double t = *A.t_in;
   double dt = A.cfl_h / m;
   if (A.t_end > 0.0) dt = fmin(dt, fmax(A.t_end - t, 0.0));
   return dt;
 }
 
-__device__ __forceinline__ double cfl_dt_from_blocks(const StageArgs& A, double* red) {
-  return cfl_dt_of_max(A, grid_max_from_blocks(A, red));
-}
+// The maximum in two parts: begin() at the start of the kernel, finish(),
+// once in every wave, where dt is needed.  Up to kOwn slots (the small
+// grids, whose time is latency) every wave reads them all for itself: begin()
+// only issues the loads and finish() needs no barrier, so the wave's first
+// cells are computed in between.  More slots are shared out over the
+// workgroup (one load per wave and slot would cost a 1024^2 grid a third of
+// its step): finish() then holds a workgroup barrier.
+struct GridMax {
+  static constexpr int kOwn = 256;
+  double own[kOwn / 64];
+  __device__ __forceinline__ void begin(const StageArgs& A, double* red) {
+    // (the last slot repeated past the end: no branch, and no wait for the
+    // loads at one)
+#pragma unroll
+    for (int q = 0; q < kOwn / 64; ++q) own[q] = A.blkmax[min((int)(threadIdx.x & 63) + 64 * q, A.nslot - 1)];
+    if (A.nslot > kOwn) {
+      double m = 0.0;
+      for (int b = threadIdx.x; b < A.nslot; b += blockDim.x) m = fmax(m, A.blkmax[b]);
+      m = wave_max(m);
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    }
+  }
+  __device__ __forceinline__ double finish(const StageArgs& A, const double* red) const {
+    if (A.nslot <= kOwn) {
+      double m = own[0];
+#pragma unroll
+      for (int q = 1; q < kOwn / 64; ++q) m = fmax(m, own[q]);
+      return wave_max(m);
+    }
+    __syncthreads();
+    double m = 0.0;
+    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) m = fmax(m, red[q]);
+    return m;
+  }
+};
 
 // Stage 2: the workgroup's largest c_tot of the new state, stored in its own
 // slot (plain store: the next stage 1 reads the slots after this kernel has
@@ -272,8 +293,9 @@ __device__ __forceinline__ void cfl_epilogue(const StageArgs& A, double* red, do
   if (threadIdx.x == 0) {
     double m = 0.0;
     for (int q = 0; q < (int)(blockDim.x >> 6); ++q) m = fmax(m, red[q]);
-    A.blkmax[blockIdx.x] = m;
-    if (blockIdx.x == 0) A.scal[kTime] = A.scal[kTime] + dt;
+    // slots past this launch's workgroups (another kernel's) hold 0
+    for (int q = blockIdx.x; q < A.nslot; q += gridDim.x) A.blkmax_out[q] = q == (int)blockIdx.x ? m : 0.0;
+    if (blockIdx.x == 0) *A.t_out = *A.t_in + dt;
   }
 }
 

@@ -3,6 +3,7 @@
 // Compiled once per (RSST_INST_NDIM, RSST_INST_ST, RSST_INST_BIG) so the
 // library builds in parallel objects; RSST_INST_BIG = 1 builds the 3D
 // kernels that address states of 2 GiB or more (Field64).
+#include "rsst_row2.h"
 #include "rsst_stage1.h"
 #include "rsst_stage2.h"
 #include "rsst_stage3.h"
@@ -43,7 +44,9 @@ __global__ void __launch_bounds__(NDIM == 3 ? kMaxThreads3 : 1024) stage_kernel(
   double dt = A.dt_fixed;
   if (!(A.dt_fixed > 0.0)) {
     if constexpr (STAGE == 1) {
-      dt = cfl_dt_from_blocks(A, lds + red);
+      GridMax gm;
+      gm.begin(A, lds + red);
+      dt = cfl_dt_of_max(A, gm.finish(A, lds + red));
       if (blockIdx.x == 0 && threadIdx.x == 0) A.scal[kDtCur] = dt;
     } else {
       dt = A.scal[kDtCur];
@@ -57,62 +60,137 @@ __global__ void __launch_bounds__(NDIM == 3 ? kMaxThreads3 : 1024) stage_kernel(
   if constexpr (STAGE == 2) cfl_epilogue(A, lds + red, cmax, dt);
 }
 
-// 2D grids: NP planes of y per march iteration (the geometry's np): two for
-// large grids with rows of up to eight waves (512 threads at most), else one
-// (up to 1024 threads, fewer registers per thread).
-template <int STAGE, typename ST, int FORM, int NP>
-__global__ void __launch_bounds__(NP == 2 ? 512 : 1024) stage_kernel2d(const StageArgs A) {
-  extern __shared__ double lds[];
-  const Geometry& G = A.geo;
-  const int L = xcd_tile(blockIdx.x, gridDim.x);
-  const int chunk_base = L * G.ts;
-  const int red = carve2(G.ts, G.nwx, NP).red;
-  double dt = A.dt_fixed;
-  if (!(A.dt_fixed > 0.0)) {
+// The step's dt in a 2D kernel: given, or (stage 1) formed from the maxima and
+// recorded for a separate stage 2.  begin() and finish() as GridMax's.
+template <int STAGE>
+struct StepDt {
+  const StageArgs& A;
+  double* red;
+  GridMax gm;
+  __device__ __forceinline__ void begin() {
     if constexpr (STAGE == 1) {
-      dt = cfl_dt_from_blocks(A, lds + red);
-      if (blockIdx.x == 0 && threadIdx.x == 0) A.scal[kDtCur] = dt;
-    } else {
-      dt = A.scal[kDtCur];
+      if (!(A.dt_fixed > 0.0)) gm.begin(A, red);
     }
   }
+  __device__ __forceinline__ double finish() const {
+    if (A.dt_fixed > 0.0) return A.dt_fixed;
+    if constexpr (STAGE == 1) {
+      const double dt = cfl_dt_of_max(A, gm.finish(A, red));
+      if (blockIdx.x == 0 && threadIdx.x == 0) A.scal[kDtCur] = dt;
+      return dt;
+    } else {
+      return A.scal[kDtCur];
+    }
+  }
+};
+
+// 2D grids, one stage: a workgroup is four independent waves, each one strip
+// of a chunk (rsst_stage2.h).  Four waves per SIMD (128 VGPRs) hide a row's
+// latencies.
+template <int STAGE, typename ST, int FORM>
+__global__ void __launch_bounds__(64 * kWaves2) __attribute__((amdgpu_waves_per_eu(4))) stage_kernel2d(
+    const StageArgs A) {
+  extern __shared__ double lds[];
+  fetch_args2(A);
+  const Geometry& G = A.geo;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int task = xcd_tile(blockIdx.x, G.nblk) * kWaves2 + w, ntask = G.cols.ncol * G.nchunk;
+  const bool work = task < ntask;
+  const int t = work ? task : ntask - 1;
+  const int k0 = (t / G.cols.ncol) * G.km;
+  const int k1 = work ? min(k0 + G.km, G.nm) : k0 + 1;
   unsigned bad = 0;
-  const double cmax = stage_body2<STAGE, ST, FORM, NP>(A, lds, chunk_base, dt, bad);
+  double dt = 0.0;
+  const Tile2 none{nullptr, 0, 0};
+  StepDt<STAGE> sd{A, lds + kRed2, {}};
+  sd.begin();
+  const double cmax = march2<kSplit, STAGE, ST, FORM>(
+      A, lane_of(G.cols, G.nx, A.bc_lo[0] == 0, t % G.cols.ncol), lds + w * kLds2, none, k0, k1, k0, k1, work,
+      [&]() { return dt = sd.finish(); }, bad);
   if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
-  if constexpr (STAGE == 2) cfl_epilogue(A, lds + red, cmax, dt);
+  if constexpr (STAGE == 2) cfl_epilogue(A, lds + kRed2, cmax, dt);
+}
+
+// 2D grids, one stage, a workgroup per whole row (rsst_row2.h): NP rows per
+// march iteration.
+template <int STAGE, typename ST, int FORM, int NP>
+__global__ void __launch_bounds__(512) row_kernel2d(const StageArgs A) {
+  extern __shared__ double lds[];
+  double* red = lds + carve2(A.geo.ts, A.geo.nwx, NP).red;
+  StepDt<STAGE> sd{A, red, {}};
+  sd.begin();
+  const double dt = sd.finish();
+  unsigned bad = 0;
+  const double cmax = stage_body2<STAGE, ST, FORM, NP>(A, lds, xcd_tile(blockIdx.x, A.geo.nblk), dt, bad);
+  if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
+  if constexpr (STAGE == 2) cfl_epilogue(A, red, cmax, dt);
+}
+
+// 2D grids, both stages of a step (rsst_stage2.h): one workgroup per CU, two
+// waves per SIMD with all the registers.
+template <typename ST, int FORM>
+__global__ void __launch_bounds__(64 * kWavesF) __attribute__((amdgpu_waves_per_eu(2, 2)))
+step_kernel2d(const StageArgs A) {
+  extern __shared__ double lds[];
+  fetch_args2(A);
+  double* red = lds + lds_doublesF(A.geo.rF) - kWavesF;
+  unsigned bad = 0;
+  double dt = 0.0;
+  StepDt<1> sd{A, red, {}};
+  sd.begin();
+  const double cmax = step_tile2<ST, FORM>(A, lds, xcd_tile(blockIdx.x, A.geo.nblkF),
+                                           [&]() { return dt = sd.finish(); }, bad);
+  if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
+  cfl_epilogue(A, red, cmax, dt);
 }
 
 // One launch of a stage kernel over the geometry's grid.  The kernel's LDS
 // limit is raised only when a larger tile needs it (lds_set: the limit set
 // so far per device, owned by the kernel's launcher), so launches of a known
 // shape (e.g. under HIP graph capture) make no attribute call.
-static hipError_t launch_geo(void (*kern)(StageArgs), int* lds_set, const StageArgs& a, hipStream_t s) {
-  const Geometry& G = a.geo;
-  const dim3 grid((unsigned)(G.ntile_s * G.nchunk)), block((unsigned)G.threads);
+static hipError_t launch_geo(void (*kern)(StageArgs), int* lds_set, int nblk, int threads, size_t lds_bytes,
+                             const StageArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)nblk), block((unsigned)threads);
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-  if ((int)G.lds_bytes > lds_set[dev]) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)G.lds_bytes);
+  if ((int)lds_bytes > lds_set[dev]) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (e != hipSuccess) return e;
-    lds_set[dev] = (int)G.lds_bytes;
+    lds_set[dev] = (int)lds_bytes;
   }
-  hipLaunchKernelGGL(kern, grid, block, G.lds_bytes, s, a);
+  hipLaunchKernelGGL(kern, grid, block, lds_bytes, s, a);
   return hipGetLastError();
 }
 
 template <int NDIM, int STAGE, typename ST, int FORM, int NWXC>
 static hipError_t launch_stage_k(const StageArgs& a, hipStream_t s) {
   static int lds_set[64] = {0};
-  return launch_geo(stage_kernel<NDIM, STAGE, ST, FORM, NWXC, kBig>, lds_set, a, s);
+  return launch_geo(stage_kernel<NDIM, STAGE, ST, FORM, NWXC, kBig>, lds_set, a.geo.nblk, a.geo.threads, a.geo.lds_bytes,
+                    a, s);
 }
 
 template <int STAGE, typename ST, int FORM, int NP>
-static hipError_t launch_stage_2d(const StageArgs& a, hipStream_t s) {
+static hipError_t launch_rows_2d(const StageArgs& a, hipStream_t s) {
   static int lds_set[64] = {0};
-  return launch_geo(stage_kernel2d<STAGE, ST, FORM, NP>, lds_set, a, s);
+  return launch_geo(row_kernel2d<STAGE, ST, FORM, NP>, lds_set, a.geo.nblk, a.geo.threads, a.geo.lds_bytes, a, s);
 }
 
+template <int STAGE, typename ST, int FORM>
+static hipError_t launch_stage_2d(const StageArgs& a, hipStream_t s) {
+  if (a.geo.rows)
+    return a.geo.np == 2 ? launch_rows_2d<STAGE, ST, FORM, 2>(a, s) : launch_rows_2d<STAGE, ST, FORM, 1>(a, s);
+  static int lds_set[64] = {0};
+  return launch_geo(stage_kernel2d<STAGE, ST, FORM>, lds_set, a.geo.nblk, a.geo.threads, a.geo.lds_bytes, a, s);
+}
+
+template <typename ST, int FORM>
+static hipError_t launch_step_2d(const StageArgs& a, hipStream_t s) {
+  static int lds_set[64] = {0};
+  return launch_geo(step_kernel2d<ST, FORM>, lds_set, a.geo.nblkF, 64 * kWavesF,
+                    (size_t)lds_doublesF(a.geo.rF) * sizeof(double), a, s);
+}
+
+// STAGE 0: both stages of a 2D step.
 template <int NDIM, int STAGE, typename ST, int FORM>
 static hipError_t launch_stage_t(const StageArgs& a, hipStream_t s) {
   if constexpr (NDIM == 3) {
@@ -125,7 +203,8 @@ static hipError_t launch_stage_t(const StageArgs& a, hipStream_t s) {
       default: return hipErrorInvalidValue;
     }
   } else if constexpr (NDIM == 2) {
-    return a.geo.np == 2 ? launch_stage_2d<STAGE, ST, FORM, 2>(a, s) : launch_stage_2d<STAGE, ST, FORM, 1>(a, s);
+    if constexpr (STAGE == 0) return launch_step_2d<ST, FORM>(a, s);
+    else return launch_stage_2d<STAGE, ST, FORM>(a, s);
   } else {
     return launch_stage_k<NDIM, STAGE, ST, FORM, 0>(a, s);
   }
@@ -174,6 +253,15 @@ hipError_t launch_stage_n(const StageArgs& a, int stage, hipStream_t s) {
   return stage == 1 ? launch_stage_f<NDIM, 1, ST>(a, s) : launch_stage_f<NDIM, 2, ST>(a, s);
 }
 
+#if RSST_INST_NDIM == 2
+template <typename ST>
+hipError_t launch_step2d(const StageArgs& a, hipStream_t s) {
+  return launch_stage_f<2, 0, ST>(a, s);
+}
+
+template hipError_t launch_step2d<RSST_INST_ST>(const StageArgs&, hipStream_t);
+#endif
+
 template hipError_t launch_stage_n<RSST_INST_NDIM, RSST_INST_ST, kBig>(const StageArgs&, int, hipStream_t);
 
 #if RSST_INST_NDIM == 1 && !RSST_INST_BIG
@@ -198,7 +286,7 @@ __global__ void __launch_bounds__(1024) steps1d_kernel(const StageArgs a1, const
   const Geometry& G = a1.geo;
   double* red = lds + carve1(G.nwx).red;
   const bool cfl = !(a1.dt_fixed > 0.0);
-  double t = a1.scal[kTime];
+  double t = *a1.t_in;
   double dt = a1.dt_fixed;
   if (cfl) {  // from the one stored maximum (a 1D grid is one workgroup), as stage 1 forms it
     dt = a1.cfl_h / a1.blkmax[0];
@@ -254,8 +342,8 @@ __global__ void __launch_bounds__(1024) steps1d_kernel(const StageArgs a1, const
   }
   if (bad) atomicOr((unsigned*)(a1.scal + kFlags), bad);
   if (threadIdx.x == 0) {
-    a1.scal[kTime] = t;
-    if (mlast >= 0.0) a1.blkmax[0] = mlast;  // the maximum of the state left in U
+    *a1.t_out = t;
+    if (mlast >= 0.0) a1.blkmax_out[0] = mlast;  // the maximum of the state left in U
   }
 }
 
@@ -290,7 +378,7 @@ static hipError_t launch_steps1d_x(const StageArgs& a1, const StageArgs& a2, int
 
 template <typename ST>
 hipError_t launch_steps1d(const StageArgs& a1, const StageArgs& a2, int nsteps, hipStream_t s) {
-  if (a1.geo.ndim != 1 || a1.geo.ntile_s * a1.geo.nchunk != 1) return hipErrorInvalidValue;
+  if (a1.geo.ndim != 1 || a1.geo.nblk != 1) return hipErrorInvalidValue;
   if constexpr (sizeof(ST) == 8) {
     if (a1.eos) return launch_steps1d_x<ST, kExtVdw>(a1, a2, nsteps, s);
   }
