@@ -249,6 +249,27 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
     load_cell_raw<NDIM, ST>(uin, k0l, chi2, o4);
   }
 
+  // publishes both rows' cell states of a plane, and the x ghosts
+  auto publish = [&](const double (&q)[2][NV]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      if (xin) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) ub[c * UR + v * PX + 1] = q[c][v];
+      }
+      if (i_raw == 0 || last_x) {
+        // cell 0: periodic, the ghost right of the last cell; wall, the
+        // mirror left of cell 0.  The last cell: periodic, the ghost left of
+        // cell 0; wall, the mirror right of the last cell.
+        double* ur = Us + (rl + c) * UR + ((i_raw == 0) == x_per ? G.nx + 1 : 0);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) ur[v * PX] = (v == 1 && !x_per) ? -q[c][v] : q[c][v];
+      }
+    }
+  };
+  publish(q0);
+  __syncthreads();
+
   for (int it = 0; it < G.km; ++it) {
     const int kraw = k0 + it;
     const bool kval = kraw < k1;
@@ -263,24 +284,6 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
     k_cur = k;
 #pragma unroll
     for (int c = 0; c < 2; ++c) load_cell_raw<NDIM, ST>(uin, q2k, colc[c], q2r[c]);
-
-    // ---- P1: publish both rows' cell states, and the x ghosts
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      if (xin) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) ub[c * UR + v * PX + 1] = q0[c][v];
-      }
-      if (i_raw == 0 || last_x) {
-        // cell 0: periodic, the ghost right of the last cell; wall, the
-        // mirror left of cell 0.  The last cell: periodic, the ghost left of
-        // cell 0; wall, the mirror right of the last cell.
-        double* ur = Us + (rl + c) * UR + ((i_raw == 0) == x_per ? G.nx + 1 : 0);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) ur[v * PX] = (v == 1 && !x_per) ? -q0[c][v] : q0[c][v];
-      }
-    }
-    __syncthreads();  // B1
 
     // ---- P2: x plus-face states (published), y face states, the y flux
     // between the thread's rows, and at the tile's outer faces
@@ -368,14 +371,17 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
       }
     };
     if constexpr (kEarlyOut) load_outside();
-    __syncthreads();  // B2
+    __syncthreads();  // B1
     if constexpr (STAGE == 2) {
 #pragma unroll
       for (int c = 0; c < 2; ++c) load_cell_raw<NDIM, ST, kUnAux3>(unp, k, colc[c], unr[c]);
     }
 
-    // ---- P3: the x flux at each cell's left face and the y flux at the
-    // thread-row's lower face, published for the cell on the other side
+    // ---- P3: the next plane's cell states (the rows just read are free), so
+    // that its P2 follows this plane's P4 with no barrier between; the x flux
+    // at each cell's left face and the y flux at the thread-row's lower face,
+    // published for the cell on the other side
+    if (it + 1 < G.km) publish(q1);
     double Fx_lo[2][NV];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
@@ -399,7 +405,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
 #pragma unroll
       for (int v = 0; v < NV; ++v) yf[v * NXP - NV * NXP] = Fy_lo[v];
     }
-    __syncthreads();  // B3
+    __syncthreads();  // B2
 
     // ---- P4: the fluxes on the far side of each cell, the z direction,
     // then the rate, the RK update and the store
