@@ -129,7 +129,7 @@ enum rsst_flag {
                             adjoint calls (FP64 only): on a 2D grid
                             nvar * ncell doubles and three per 16 x 16 tile,
                             else nvar * ncell * (2 ndim + 3) doubles and four
-                            per 256 cells.  The adjoint calls of one handle
+                            per 256 cells (128 in 3D up to 131072 cells).  The adjoint calls of one handle
                             share it: order them on one stream.               */
 };
 

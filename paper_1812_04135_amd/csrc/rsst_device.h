@@ -285,6 +285,14 @@ __device__ __forceinline__ double cell_ctot(const double (&u)[NDIM + 2], const C
   else return fma(sqrt_nr(a2), K.inv_xi, sqrt_nr(v2));
 }
 
+// Tile id -> XCD: dispatch is round-robin over the 8 XCDs, so consecutive
+// tiles (which share halo rows) are remapped onto one XCD and its L2.  XCD x
+// gets nblk / 8 consecutive tiles, one more for x < nblk % 8.
+__device__ __forceinline__ int xcd_tile(int b, int nblk) {
+  const int x = b & 7, per = nblk >> 3;
+  return x * per + min(x, nblk & 7) + (b >> 3);
+}
+
 // ---- cross-lane moves (wave64 DPP) -------------------------------------
 
 // Value held by lane l-1 (lane 0 receives 0: with bound_ctrl set the

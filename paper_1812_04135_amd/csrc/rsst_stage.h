@@ -226,14 +226,6 @@ __device__ __forceinline__ Face<NV> face_from_left(const Face<NV>& s) {
   return r;
 }
 
-// Tile id -> XCD: dispatch is round-robin over the 8 XCDs, so consecutive
-// tiles (which share halo rows) are remapped onto one XCD and its L2.  XCD x
-// gets nblk / 8 consecutive tiles, one more for x < nblk % 8.
-__device__ __forceinline__ int xcd_tile(int b, int nblk) {
-  const int x = b & 7, per = nblk >> 3;
-  return x * per + min(x, nblk & 7) + (b >> 3);
-}
-
 // CFL step from the maxima of c_tot that the last stage 2 (or the prime
 // kernel) stored per workgroup: dt = cfl h / max, cut at t_end.  Formed by
 // every workgroup of stage 1, the same bits in each (a maximum does not
