@@ -53,7 +53,7 @@ class RSSTRollout(torch.autograd.Function):
             out = U0.detach().contiguous().clone()
             if nsteps > 0:
                 traj[0].copy_(out)
-                solver.steps_out([traj[n] for n in range(nsteps)] + [out], [stage1[n] for n in range(nsteps)], dt)
+                solver.steps_out(_step_ptrs(traj, nsteps) + [out], _step_ptrs(stage1, nsteps), dt)
             ctx.traj, ctx.stage1, ctx.ckpts = traj, stage1, None
             return out
         U = U0.detach().contiguous().clone()
@@ -82,8 +82,7 @@ class RSSTRollout(torch.autograd.Function):
         lam = gU.detach().to(torch.float64).contiguous().clone()
         dxi = torch.zeros(1, dtype=torch.float64, device=lam.device)
         if K == 1:
-            solver.adjoint_run([ctx.traj[n] for n in range(nsteps)], [ctx.stage1[n] for n in range(nsteps)],
-                               lam, dt, dxi)
+            solver.adjoint_run(_step_ptrs(ctx.traj, nsteps), _step_ptrs(ctx.stage1, nsteps), lam, dt, dxi)
             torch.cuda.synchronize()
             solver.close()
             ctx.traj = ctx.stage1 = None
@@ -123,6 +122,13 @@ class RSSTRollout(torch.autograd.Function):
         ctx.ckpts = None
         gxi = dxi.reshape(()) if ctx.xi_needs_grad else None
         return lam, gxi, None, None, None, None, None
+
+
+def _step_ptrs(buf, nsteps):
+    """Device addresses of the states buf[0], .. buf[nsteps - 1] of a kept
+    trajectory (a view per state costs about a microsecond each)."""
+    base, size = buf.data_ptr(), buf[0].numel() * buf.element_size()
+    return [base + n * size for n in range(nsteps)]
 
 
 def trajectory_or_interval(U0, nsteps, checkpoint_every):

@@ -159,3 +159,19 @@ def test_batch_boxes_equal_single_runs(sizes, prec):
         P0 = pert[q].astype(np.float32) if prec == "fp32_pert" else pert[q]
         ref, tr, _, _ = _run(cfg, P0, "step", 12, **kw)
         assert np.array_equal(got[q], ref) and t[q] == tr, (q, sizes[q])
+
+
+def test_reused_workspace_starts_clean():
+    """A solver made after another was closed may take its workspace: its
+    results are those of a first solver, also from a larger or a smaller
+    block, with an adjoint workspace or not, and with two alive at once."""
+    cases = [_case(n, PER, None, "pvs", {}) for n in ([64, 40], [60, 40], [80, 41], [64, 40])]
+    refs = []
+    for cfg, U0 in cases:
+        refs.append(_run(cfg, U0, "steps", 5))
+    for rep in range(3):
+        for (cfg, U0), ref in zip(cases, refs):
+            other = R.Solver(cases[rep][0], adjoint=rep == 1)
+            got = _run(cfg, U0, "steps", 5)
+            other.close()
+            assert np.array_equal(got[0], ref[0]) and got[1:] == ref[1:]
