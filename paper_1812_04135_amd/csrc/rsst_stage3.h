@@ -267,8 +267,6 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
       }
     }
   };
-  publish(q0);
-  __syncthreads();
 
   for (int it = 0; it < G.km; ++it) {
     const int kraw = k0 + it;
@@ -284,6 +282,11 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
     k_cur = k;
 #pragma unroll
     for (int c = 0; c < 2; ++c) load_cell_raw<NDIM, ST>(uin, q2k, colc[c], q2r[c]);
+
+    if (it == 0) {
+      publish(q0);
+      __syncthreads();
+    }
 
     // ---- P2: x plus-face states (published), y face states, the y flux
     // between the thread's rows, and at the tile's outer faces
