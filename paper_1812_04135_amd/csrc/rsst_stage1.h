@@ -243,4 +243,45 @@ __device__ __forceinline__ double stage_body1(const StageArgs& A, double* lds, d
   return cmax;
 }
 
+// ---- every step of a run in one launch, by waves with halo lanes -----------
+//
+// A run of 1D steps is one workgroup and bound by the latency of a step: the
+// chain through two stages, the maximum and dt.  stage_body1 exchanges at wave
+// edges through LDS and takes seven barriers per step.  Here each wave holds
+// up to 56 cells and four more on each side, which both stages of a step use
+// up, so the two stages run in registers with neighbours by DPP alone; then
+// the waves publish their cells and maxima and meet at the step's one barrier.
+// A wall's ghost lane is the mirror of its cell, with m_x and the force
+// negated: every expression below then gives the mirror image, so it stays
+// one.  us per step with the barriers and so (PVS, FP64): 64 cells 2.65, 1.31;
+// 224 cells 3.08, 1.37; 256 cells 3.05, 2.11 (five waves, two of them on one
+// SIMD); 896 cells 6.38, 3.80.
+constexpr int kHalo1 = 4;
+constexpr int kTile1 = 64 - 2 * kHalo1;   // cells per wave
+constexpr int kMaxHalo1 = 16 * kTile1;    // longest row of such a run (16 waves)
+
+// One stage of a wave's lanes: u (the stage input) -> y = u + dt R(u), with
+// the non-physical flags of u.  Lanes whose neighbours are unknown give
+// nothing of use: two more at each end of the wave per stage.
+template <int FORMX>
+__device__ __forceinline__ unsigned lane_stage1(const double (&u)[3], const Consts& K, const double (&g)[3], double hx,
+                                                double dt, double (&y)[3]) {
+  constexpr int NDIM = 1, NV = 3;
+  constexpr int FORM = FORMX & 7;
+  constexpr int EXT = FORMX & (kExtCmax | kExtVdw);
+  double h[NV], Fx_lo[NV], Dl[NV], R[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) h[v] = mc_half(u[v] - from_left(u[v]), from_right(u[v]) - u[v]);
+  Face<NV> fm, fp;
+  make_face<NDIM, 0, EXT>(u, h, false, K, fm);
+  make_face<NDIM, 0, EXT>(u, h, true, K, fp);
+  flux2<NDIM, 0>(face_from_left(fp), fm, Fx_lo);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) Dl[v] = -(from_right(Fx_lo[v]) - Fx_lo[v]) * hx;
+  const unsigned b = rsst_rate<NDIM, FORM, EXT>(u, Dl, K, g, R);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) y[v] = fma(dt, R[v], u[v]);
+  return b;
+}
+
 }  // namespace rsstk

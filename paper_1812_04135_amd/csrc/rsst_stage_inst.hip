@@ -347,9 +347,123 @@ __global__ void __launch_bounds__(1024) steps1d_kernel(const StageArgs a1, const
   }
 }
 
+// The same run by waves with halo lanes (rsst_stage1.h), rows of at most
+// kMaxHalo1 cells: LDS holds the cells and the waves' maxima twice, by the
+// parity of the step, so that one barrier per step orders a step's writes
+// before its reads and those before the writes two steps on.  The same bits.
+template <typename ST, int FORM>
+__global__ void __launch_bounds__(1024) steps1d_halo_kernel(const StageArgs A, int nsteps) {
+  constexpr int NV = 3;
+  constexpr int EXT = FORM & (kExtCmax | kExtVdw);
+  constexpr bool F32 = sizeof(ST) == 4;
+  extern __shared__ double lds[];
+  const int nx = A.geo.nx, nw = blockDim.x >> 6, cw = (nx + nw - 1) / nw;
+  double* const cells = lds;                 // [2][NV][nx]
+  double* const maxima = lds + 2 * NV * nx;  // [2][nw]
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool x_per = A.bc_lo[0] == 0;
+  // the lane's cell, and whether it is a wall's ghost
+  const int x0 = w * cw, q = min(x0 + lane - kHalo1, nx + kHalo1 - 1);
+  const int i = q < 0 ? (x_per ? q + nx : -1 - q) : (q >= nx ? (x_per ? q - nx : 2 * nx - 1 - q) : q);
+  const bool ghost = !x_per && (q < 0 || q >= nx);
+  const bool own = lane >= kHalo1 && lane < kHalo1 + min(cw, nx - x0);
+  const int flip = ghost ? (int)0x80000000 : 0;
+  auto mirrored = [&](double x) { return __hiloint2double(__double2hiint(x) ^ flip, __double2loint(x)); };
+  const Consts K{A.gamma, A.gm1, A.inv_gm1, A.inv_xi, A.f, A.inv_cmax2, A.vdw_a, A.vdw_b};
+  const double g[3] = {mirrored(A.g[0]), 0.0, 0.0};
+  const double hx = 0.5 * A.inv_dx[0];
+  double bg[NV] = {}, u[NV], st[NV] = {};
+  const ST* in = (const ST*)A.uin;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    if constexpr (F32) bg[v] = A.bg[v * A.nbg + (A.bg_axis == 0 ? i : 0)];
+    u[v] = (double)in[v * A.ncell + i];
+    if constexpr (F32) u[v] += bg[v];
+  }
+  u[1] = mirrored(u[1]);
+  const bool cfl = !(A.dt_fixed > 0.0);
+  double t = *A.t_in, dt = A.dt_fixed;
+  double m = A.blkmax[0], mlast = -1.0;
+  unsigned bad = 0;
+  for (int n = 0; n < nsteps; ++n) {
+    if (cfl) {
+      dt = A.cfl_h / m;
+      if (A.t_end > 0.0) {
+        dt = fmin(dt, fmax(A.t_end - t, 0.0));
+        if (!(dt > 0.0)) break;
+      }
+    }
+    // a lane's stored value and what the next stage reads back from it
+    // (rounded to the storage type; a ghost's rounds to its cell's mirror
+    // image: its background momentum is its cell's)
+    double y[NV], u1[NV];
+    unsigned b = lane_stage1<FORM>(u, K, g, hx, dt, y);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      if constexpr (F32) {
+        const double x = v == 1 ? mirrored(y[v]) : y[v];
+        const double r = (double)(ST)(x - bg[v]) + bg[v];
+        u1[v] = v == 1 ? mirrored(r) : r;
+      } else {
+        u1[v] = y[v];
+      }
+    }
+    b |= lane_stage1<FORM>(u1, K, g, hx, dt, y);
+    double out[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      y[v] = 0.5 * (u[v] + y[v]);
+      const ST r = (ST)(y[v] - bg[v]);
+      st[v] = (double)r;
+      if constexpr (F32) out[v] = st[v] + bg[v];
+      else out[v] = y[v];
+    }
+    if (own) bad |= b;
+    // publish the new cells and the wave's largest c_tot, then read the cell
+    // (a halo lane's from the wave that owns it) and the maxima
+    double* const c = cells + (n & 1) * NV * nx;
+    double* const mx = maxima + (n & 1) * nw;
+    const double wm = wave_max(own ? cell_ctot<1, EXT>(out, K) : 0.0);
+    if (own) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) c[v * nx + i] = out[v];
+    }
+    if (lane == 0) mx[w] = wm;
+    t = t + dt;
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NV; ++v) u[v] = c[v * nx + i];
+    u[1] = mirrored(u[1]);
+    m = 0.0;
+    for (int k = 0; k < nw; ++k) m = fmax(m, mx[k]);
+    mlast = m;
+  }
+  if (mlast >= 0.0 && own) {
+    ST* out = (ST*)A.uout;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[v * A.ncell + i] = (ST)st[v];
+  }
+  if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
+  if (threadIdx.x == 0) {
+    *A.t_out = t;
+    if (mlast >= 0.0) A.blkmax_out[0] = mlast;  // the maximum of the state left in U
+  }
+}
+
+template <typename ST, int FORM>
+static hipError_t launch_steps1d_halo(const StageArgs& a1, const StageArgs& a2, int nsteps, hipStream_t s) {
+  const int nw = (a1.geo.nx + kTile1 - 1) / kTile1;
+  const size_t lds = (size_t)(2 * 3 * a1.geo.nx + 2 * nw) * sizeof(double);  // at most 43 KiB
+  StageArgs a = a1;
+  a.uout = a2.uout;
+  hipLaunchKernelGGL((steps1d_halo_kernel<ST, FORM>), dim3(1), dim3((unsigned)(64 * nw)), lds, s, a, nsteps);
+  return hipGetLastError();
+}
+
 template <typename ST, int FORM>
 static hipError_t launch_steps1d_k(const StageArgs& a1, const StageArgs& a2, int nsteps, hipStream_t s) {
   const Geometry& G = a1.geo;
+  if (G.nx <= kMaxHalo1) return launch_steps1d_halo<ST, FORM>(a1, a2, nsteps, s);
   auto kern = steps1d_kernel<ST, FORM>;
   static int lds_set[64] = {0};
   int dev = 0;
