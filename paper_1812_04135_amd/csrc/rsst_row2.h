@@ -44,9 +44,10 @@ __host__ __device__ inline Carve2 carve2(int ts, int nwx, int np) {
 // non-physical flags into `bad`.  Every row of the workgroup runs the same
 // number of march iterations, so rows of different chunks share the
 // workgroup's barriers; planes past a chunk's end are computed on rows held
-// in range and not stored.
-template <int STAGE, typename ST, int FORMX, int NP>
-__device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, int chunk_base, double dt,
+// in range and not stored.  dtf() gives the step's dt; it is called once, after
+// the first rows are loaded.
+template <int STAGE, typename ST, int FORMX, int NP, typename DtFn>
+__device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, int chunk_base, DtFn dtf,
                                               unsigned& bad) {
   constexpr int NDIM = 2, NV = 4, PL = NV + 3;
   constexpr int FORM = FORMX & 7;
@@ -151,6 +152,7 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
     make_face<NDIM, 1, EXT>(q0, sm0, false, K, fr);
     flux2<NDIM, 1>(fl, fr, Fm_lo);
   }
+  const double dt = dtf();
 
   for (int it = 0; it < G.km; it += NP) {
     const int kraw = k0 + it;

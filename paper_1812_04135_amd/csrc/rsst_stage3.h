@@ -59,10 +59,11 @@ __host__ __device__ inline Carve3 carve3(int ts, int nwx) {
 // tile of a column whose height is not a multiple of TS is moved down to end
 // at the last row: its rows below tile_s TS are computed (with the same bits)
 // but stored by the tile before it.  NWXC: waves per x row (rows of five to
-// eight waves run as rows of eight); BIG: Field64 addressing.
-template <int STAGE, typename ST, int FORMX, int NWXC, bool BIG = false>
+// eight waves run as rows of eight); BIG: Field64 addressing.  dtf() gives the
+// step's dt; it is called once, after the first planes' loads are issued.
+template <int STAGE, typename ST, int FORMX, int NWXC, bool BIG = false, typename DtFn>
 __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, int tile_s, int chunk,
-                                              double dt, unsigned& bad) {
+                                              DtFn dtf, unsigned& bad) {
   constexpr int NDIM = 3, NV = 5, PL = NV + 3;
   constexpr int FORM = FORMX & 7;
   constexpr int EXT = FORMX & (kExtCmax | kExtVdw);
@@ -248,6 +249,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
     load_cell_raw<NDIM, ST>(uin, k0l, chi1, o3);
     load_cell_raw<NDIM, ST>(uin, k0l, chi2, o4);
   }
+  const double dt = dtf();
 
   // publishes both rows' cell states of a plane, and the x ghosts
   auto publish = [&](const double (&q)[2][NV]) {

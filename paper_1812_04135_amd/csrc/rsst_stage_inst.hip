@@ -30,37 +30,7 @@ constexpr int kMaxThreads3 = 512;
 
 constexpr bool kBig = RSST_INST_BIG != 0;
 
-template <int NDIM, int STAGE, typename ST, int FORM, int NWXC, bool BIG>
-__global__ void __launch_bounds__(NDIM == 3 ? kMaxThreads3 : 1024) stage_kernel(const StageArgs A) {
-  extern __shared__ double lds[];
-  const Geometry& G = A.geo;
-  const int L = xcd_tile(blockIdx.x, gridDim.x);
-  const int tile_s = L % G.ntile_s;
-  const int chunk_base = (L / G.ntile_s) * (NDIM == 3 ? 1 : G.ts);
-  static_assert(NDIM != 2, "2D grids run stage_kernel2d");
-  const int red = NDIM == 3 ? carve3(G.ts, NWXC).red : carve1(G.nwx).red;
-  // a CFL step's dt: formed by stage 1 from the maxima of the state it
-  // reads, recorded for stage 2
-  double dt = A.dt_fixed;
-  if (!(A.dt_fixed > 0.0)) {
-    if constexpr (STAGE == 1) {
-      GridMax gm;
-      gm.begin(A, lds + red);
-      dt = cfl_dt_of_max(A, gm.finish(A, lds + red));
-      if (blockIdx.x == 0 && threadIdx.x == 0) A.scal[kDtCur] = dt;
-    } else {
-      dt = A.scal[kDtCur];
-    }
-  }
-  unsigned bad = 0;
-  double cmax;
-  if constexpr (NDIM == 3) cmax = stage_body3<STAGE, ST, FORM, NWXC, BIG>(A, lds, tile_s, chunk_base, dt, bad);
-  else cmax = stage_body1<STAGE, ST, FORM>(A, lds, dt, bad);
-  if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
-  if constexpr (STAGE == 2) cfl_epilogue(A, lds + red, cmax, dt);
-}
-
-// The step's dt in a 2D kernel: given, or (stage 1) formed from the maxima and
+// The step's dt: given, or (stage 1) formed from the maxima and
 // recorded for a separate stage 2.  begin() and finish() as GridMax's.
 template <int STAGE>
 struct StepDt {
@@ -83,6 +53,28 @@ struct StepDt {
     }
   }
 };
+
+template <int NDIM, int STAGE, typename ST, int FORM, int NWXC, bool BIG>
+__global__ void __launch_bounds__(NDIM == 3 ? kMaxThreads3 : 1024) stage_kernel(const StageArgs A) {
+  extern __shared__ double lds[];
+  static_assert(NDIM != 2, "2D grids run stage_kernel2d");
+  const Geometry& G = A.geo;
+  double* red = lds + (NDIM == 3 ? carve3(G.ts, NWXC).red : carve1(G.nwx).red);
+  StepDt<STAGE> sd{A, red, {}};
+  sd.begin();
+  unsigned bad = 0;
+  double cmax, dt = 0.0;
+  if constexpr (NDIM == 3) {
+    const int L = xcd_tile(blockIdx.x, G.nblk);
+    cmax = stage_body3<STAGE, ST, FORM, NWXC, BIG>(A, lds, L % G.ntile_s, L / G.ntile_s,
+                                                   [&]() { return dt = sd.finish(); }, bad);
+  } else {
+    dt = sd.finish();
+    cmax = stage_body1<STAGE, ST, FORM>(A, lds, dt, bad);
+  }
+  if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
+  if constexpr (STAGE == 2) cfl_epilogue(A, red, cmax, dt);
+}
 
 // 2D grids, one stage: a workgroup is four independent waves, each one strip
 // of a chunk (rsst_stage2.h).  Four waves per SIMD (128 VGPRs) hide a row's
@@ -119,9 +111,10 @@ __global__ void __launch_bounds__(512) row_kernel2d(const StageArgs A) {
   double* red = lds + carve2(A.geo.ts, A.geo.nwx, NP).red;
   StepDt<STAGE> sd{A, red, {}};
   sd.begin();
-  const double dt = sd.finish();
   unsigned bad = 0;
-  const double cmax = stage_body2<STAGE, ST, FORM, NP>(A, lds, xcd_tile(blockIdx.x, A.geo.nblk), dt, bad);
+  double dt = 0.0;
+  const double cmax = stage_body2<STAGE, ST, FORM, NP>(A, lds, xcd_tile(blockIdx.x, A.geo.nblk),
+                                                       [&]() { return dt = sd.finish(); }, bad);
   if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
   if constexpr (STAGE == 2) cfl_epilogue(A, red, cmax, dt);
 }
