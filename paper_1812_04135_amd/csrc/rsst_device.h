@@ -320,6 +320,20 @@ __device__ __forceinline__ double dpp_or_own(double x) {
                           __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
 }
 
+// The wave's issue priority (0 .. 3), lowered as the wave gets further between
+// two barriers: of the waves that share a SIMD the one that is behind issues
+// first, so they arrive together.  Without it the oldest wave runs ahead, and
+// the last is left alone with its dependent FP64 operations (8 cycles each,
+// issued every 4): 3D, two waves per SIMD, us per step, before and now: 256^3
+// 1018, 990; with FP32 storage 1059, 975; 187 x 141 x 230 545, 495; 64^3
+// 30.4, 29.5.
+__device__ __forceinline__ void wave_prio(int p) {
+  if (p >= 3) __builtin_amdgcn_s_setprio(3);
+  else if (p == 2) __builtin_amdgcn_s_setprio(2);
+  else if (p == 1) __builtin_amdgcn_s_setprio(1);
+  else __builtin_amdgcn_s_setprio(0);
+}
+
 // Maximum over the wave, in every lane: rows of 16 lanes by row shifts, then
 // lane 15 of each row and lane 31 broadcast onward, so lane 63 holds it (six
 // steps in registers; the LDS crossbar would take ~120 cycles for each).

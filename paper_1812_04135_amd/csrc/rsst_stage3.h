@@ -295,6 +295,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
     double h[2][NV];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
+      wave_prio(3 - c);
 #pragma unroll
       for (int v = 0; v < NV; ++v)
         h[c][v] = mc_half(q0[c][v] - ub[c * UR + v * PX], ub[c * UR + v * PX + 2] - q0[c][v]);
@@ -304,6 +305,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
       if (x_per && last_x) put_face(FPs + (rl + c) * FR, PX, fp);  // the periodic ghost left of cell 0
     }
     double hl[NV], Fym[NV], Fy_lo[NV], Fy_hi[NV];
+    wave_prio(1);
     {
       double uD[NV], uU[NV], d[NV], hh[NV];
       if (first) {
@@ -331,6 +333,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
         make_face<NDIM, 1, EXT>(q0[1], hh, false, K, b);
         flux2<NDIM, 1>(a, b, Fym);
       }
+      wave_prio(0);
       Face<NV> fyp;
       make_face<NDIM, 1, EXT>(q0[1], hh, true, K, fyp);
       if (!last) put_face(yp, NXP, fyp);
@@ -390,6 +393,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
     double Fx_lo[2][NV];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
+      wave_prio(3 - c);
       Face<NV> fm, pl;
       make_face<NDIM, 0, EXT>(q0[c], h[c], false, K, fm);
       get_face(fb + c * FR, PX, pl);  // slot i: the plus face of cell i - 1
@@ -402,6 +406,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
         for (int v = 0; v < NV; ++v) xs[(c * NV + v) * NWXC] = Fx_lo[c][v];
       }
     }
+    wave_prio(1);
     if (!first) {
       Face<NV> fm, pd;
       make_face<NDIM, 1, EXT>(q0[0], hl, false, K, fm);
@@ -414,6 +419,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
 
     // ---- P4: the fluxes on the far side of each cell, the z direction,
     // then the rate, the RK update and the store
+    wave_prio(3);
     double Dl[2][NV];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
@@ -455,6 +461,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
       } else {
         fin_idx(q2r[c], q2neg, 0, q2lev, q2[c]);
       }
+      wave_prio(2 - 2 * c);
       double sm1[NV], Fm_hi[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) sm1[v] = mc_half(q1[c][v] - q0[c][v], q2[c][v] - q1[c][v]);
@@ -469,6 +476,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
         sm0[c][v] = sm1[v];
       }
       double Rt[NV];
+      if (c == 0) wave_prio(1);
       const unsigned b = rsst_rate<NDIM, FORM, EXT>(q0[c], Dl[c], K, g, Rt);
       double un[NV];
       if constexpr (STAGE == 2) {
