@@ -31,6 +31,12 @@ __host__ __device__ constexpr int tile_rows3(int nwx) {
   return nwx == 1 ? 16 : (nwx == 2 ? 8 : (nwx <= 4 ? 4 : 2));
 }
 
+// Memory that no kernel writes while it is read here: loads at a uniform
+// address go through the scalar cache.  As vector loads the five values of a
+// plane's background returned after every march load issued before them (vector
+// loads complete in order); 256^3 with FP32 storage, us per step: 971, 949.
+typedef const double __attribute__((address_space(4))) * ConstF64;
+
 // LDS carve-up of a 3D workgroup (doubles); ts rows of nwx waves each.
 struct Carve3 {
   int u, fp, fyp, fy, fxs, red, total;
@@ -114,7 +120,7 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
   // held across the march (ten FP64 values per plane would take 40 VGPRs).
   // bg_at(kk, b): the lower cell's background at plane kk.  Uniform or along
   // z, its index is the same for the whole workgroup and the load goes
-  // through the scalar cache into SGPRs; along x it is the thread's column
+  // through the scalar cache into SGPRs (ConstF64); along x it is the thread's column
   // (vector loads, L1 hits).  With a profile along y the upper cell and the
   // rows outside the tile take the indexed path.
   const bool bg_on_m = F32 && A.bg_axis == 2;
@@ -124,8 +130,9 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
   auto bg_at = [&](int kk, double (&b)[NV]) {
     if (A.bg_uniform) {
       const int u = __builtin_amdgcn_readfirstlane(A.bg_axis == 2 ? kk : 0);
+      const ConstF64 bgs = (ConstF64)(uintptr_t)A.bg;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) b[v] = A.bg[v * A.nbg + u];
+      for (int v = 0; v < NV; ++v) b[v] = bgs[v * A.nbg + u];
     } else {
       load_bg<NV>(bgr, A.nbg, bg_cell(0), b);
     }
