@@ -28,7 +28,7 @@
 // only (the first whose workgroup comes to it; the hardware register XCC_ID
 // tells a workgroup its XCD): every wait is between CUs that share an L2,
 // which a store reaches before it is counted complete and which agent-scope
-// loads read past the CU's own cache.  The same run then takes 14.1 ms (20.5
+// loads read past the CU's own cache.  The same run then takes 14.0 ms (20.6
 // Gcell-updates/s; 32-row strips 13.3 ms, against 21.7 ms for the best strips
 // before), bound by FP64 issue: 0.8 of the rate at which a SIMD can issue the
 // ~390 instructions of a row (rsst_stage2.h).  Where the boxes are too few or too

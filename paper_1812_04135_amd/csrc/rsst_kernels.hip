@@ -20,7 +20,7 @@
 //     LDS rows with a ghost slot at each end (periodic wrap or mirror); every
 //     x flux is formed once, by the cell right of the face, and reaches the
 //     cell on its left by DPP within a wave and through one LDS seam value per
-//     wave edge after a third barrier (rsst_row2.h, rsst_stage3.h).  1D keeps
+//     wave edge after another barrier (rsst_row2.h, rsst_stage3.h).  1D keeps
 //     its row in one workgroup with DPP neighbours and LDS seams, the
 //     wave-edge fluxes formed by both waves (rsst_stage1.h);
 //   * 3D: each thread owns two adjacent y rows of its column, and a tile of
@@ -214,8 +214,9 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
     // rows (it re-reads four and forms one extra face to start), a row 1.05
     // us on a SIMD of its own and 0.8 us where waves share one (1024 SIMDs),
     // and the slowest SIMD decides: the cheapest km.  Measured against the
-    // best of 16 lengths: 22.3 us per step (km 5) at 512^2, best 22.3; 54.2
-    // (10) at 1024^2, best 54.2; 133 (10) at 1000 x 3000, best 131
+    // best of 16 lengths when the rule was made: 22.3 us per step (km 5) at
+    // 512^2, best 22.3; 54.2 (10) at 1024^2, best 54.2; 133 (10) at 1000 x
+    // 3000, best 131 (the last two now take 49 and 110)
     G.cols = plan_cols2(G.nx, x_per, 2);
     int km = 1;
     double best = 1e300;
@@ -228,7 +229,8 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
     // per row) where strips would need more waves and the grid has at most
     // four waves per SIMD: the step is then mostly latency, and the strips'
     // extra waves sit on some SIMDs only (us per step: 256^2 12.6, with strips
-    // 14.1; 512^2 21.2 and 23.1; but 1024^2 62 and 50, 389 x 301 25 and 17.6).
+    // 14.1; 512^2 21.2 and 23.1; but 1024^2 62 and 50, 389 x 301 25 and 17.6;
+    // since dt is formed behind the first loads 256^2 takes 11.2, 512^2 19.4).
     // Two rows per iteration where that still gives every SIMD two waves.
     G.rows = G.cols.ncol > G.nwx && (long long)G.nwx * G.nm <= 4096 && G.nwx <= 8;
     if (G.rows) {
@@ -255,8 +257,8 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
     // 1, r of stage 2): the smallest r that needs one round.  It saves a
     // launch, the stage's start-up and the way of U1 through memory, and
     // repeats the halo: with one tile per CU it is the faster one (us per
-    // step, against one stage per launch: 64^2 8.5 and 9.7, 389 x 301 14.1 and
-    // 16.5, 512^2 19.5 and 20.0, 700 x 500 21.3 and 24.1), with more the tiles'
+    // step, against one stage per launch: 64^2 8.5 and 9.7, 389 x 301 13.9 and
+    // 16.4, 512^2 18.8 and 19.4, 700 x 500 21.3 and 24.1), with more the tiles'
     // start-ups come one after the other (1024^2: 56 and 50)
     G.colsF = plan_cols2(G.nx, x_per, 4);
     G.rF = 1;
@@ -281,7 +283,7 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
     // (a chunk re-reads 4 planes and forms one extra face): the cheapest km.
     // (Halving 128 planes until there were 256 workgroups left 187 x 141 x 230
     // at 288, two rounds of 32 planes where one of 33 does: FP32 1.04 ms per
-    // step, 0.55 ms now.)
+    // step, 0.55 with it.)
     int km = 1;
     double best = 1e300;
     for (int q = 1; q <= 128 && q <= G.nm; ++q) {

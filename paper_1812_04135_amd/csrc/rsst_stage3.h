@@ -12,7 +12,7 @@
 // ghost slot at each end (periodic wrap or mirror), so no lane of a wave is
 // special except at the row's two ends.  Every x and y face flux is formed
 // once, by the cell above (or right of) the face, and handed to the cell
-// below (left) through LDS after a third barrier (x: by DPP within a wave,
+// below (left) through LDS after a second barrier (x: by DPP within a wave,
 // one LDS seam value per wave edge); the y flux at a tile's outer face is
 // formed by each of the two tiles that share it, from the same face states
 // with the same code, so with the same bits.  z is marched as in the other
@@ -120,8 +120,8 @@ __device__ __forceinline__ double stage_body3(const StageArgs& A, double* lds, i
   // held across the march (ten FP64 values per plane would take 40 VGPRs).
   // bg_at(kk, b): the lower cell's background at plane kk.  Uniform or along
   // z, its index is the same for the whole workgroup and the load goes
-  // through the scalar cache into SGPRs (ConstF64); along x it is the thread's column
-  // (vector loads, L1 hits).  With a profile along y the upper cell and the
+  // through the scalar cache into SGPRs (ConstF64); along x it is the thread's
+  // column (vector loads, L1 hits).  With a profile along y the upper cell and the
   // rows outside the tile take the indexed path.
   const bool bg_on_m = F32 && A.bg_axis == 2;
   const bool bg_rows = F32 && A.bg_axis == 1;
