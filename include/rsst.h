@@ -234,8 +234,7 @@ int rsst_destroy(rsst_handle h);
  * non-physical flags (as rsst_poll's).  Scratch (device scalars, CFL maxima
  * and the stage buffer U1) is a fixed 64 MiB device array of the library,
  * held by each device it runs on until the process ends.  It takes a copy
- * of the state, nvar * ncell * sizeof(value) bytes, plus 256 B of scalars
- * and 8 B per stage-kernel workgroup (each part rounded up to 256 B); a
+ * of the state, nvar * ncell * sizeof(value) bytes, plus 512 B; a
  * configuration that needs more than 64 MiB (a 2D 1024^2 FP64 state needs
  * 32 MiB, a 3D 128^3 FP32 perturbation 40 MiB) gives RSST_E_SCRATCH before
  * any device call.  Calls no allocating routine; enqueues only

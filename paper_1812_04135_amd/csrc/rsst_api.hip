@@ -235,11 +235,17 @@ static void use_scalars(StageArgs& a, double* scal, double* blkmax) {
 // lives in one file-scope device array of fixed size instead of a handle's
 // workspace.  Each device holds its own copy for the life of the process;
 // every call on a device reuses it, so calls that overlap on one device race.
+// Which states fit is decided by the state's size alone (kScratchBytes, less
+// one 256-byte line each for the scalars and the first maxima): how many
+// workgroups a launch has, and so how many maxima, is the planner's business.
+// The maxima past that line lie in kSlackBytes more; the most that a state of
+// this size needs is 105 KB (13107 tiles of a 3D grid of four planes).
 // In host code `scratch` only names the symbol: its device address, per
 // device, comes from hipGetSymbolAddress (taken once per device, with that
 // device current) and only that address reaches the kernels.
 static constexpr size_t kScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static constexpr size_t kSlackBytes = (size_t)128 << 10;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kSlackBytes];
 static constexpr int kMaxDevices = 64;
 static std::atomic<unsigned char*> g_scratch[kMaxDevices];
 
@@ -649,11 +655,12 @@ int rsst_step_noalloc(const rsst_config* cfg, void* U, double dt_fixed, uint32_t
   const size_t elem = cfg->prec == RSST_FP32_PERT ? sizeof(float) : sizeof(double);
   StageArgs a;
   fill_args(cfg, ncell, a);
+  a.nslot = a.geo.nblk;  // one stage per launch
   // scratch layout: scalars | CFL maxima | U1, each 256-byte aligned
   const size_t o_blk = round256(rsstk::kNumScalars * sizeof(double));
   const size_t o_u1 = o_blk + round256((size_t)a.nslot * sizeof(double));
-  const size_t need = o_u1 + (size_t)(cfg->ndim + 2) * (size_t)ncell * elem;
-  if (need > kScratchBytes) return RSST_E_SCRATCH;
+  const size_t state = (size_t)(cfg->ndim + 2) * (size_t)ncell * elem;
+  if (o_blk + 256 + state > kScratchBytes || o_u1 + state > sizeof(scratch)) return RSST_E_SCRATCH;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return RSST_E_DEVICE;
   unsigned char* base = nullptr;
