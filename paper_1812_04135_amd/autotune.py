@@ -9,8 +9,8 @@ mix of sizes and the precision, so it is measured: coordinate sweeps over
 the four width classes (repeated from the result while they change it, at
 most `passes`), each candidate timed on whole runs of the caller's batch (HIP events on the launch stream, best of `reps`), on a scratch copy
 of the state so the caller's state is not advanced.  Results are cached in a
-JSON file keyed by device, precision, form and the batch's width/height
-histogram.
+JSON file keyed by library revision (other kernels have other best lengths),
+device, precision, form and the batch's width/height/strip histogram.
 """
 from __future__ import annotations
 
@@ -25,19 +25,34 @@ def width_class(nx: int) -> int:
     return (int(nx) + 63) // 64 - 1
 
 
+def row_strips(nx: int, x_periodic: bool) -> int:
+    """Strips of a box row (as the batched kernel cuts it): one where a
+    periodic row fits a wave, else strips of at most 60 cells."""
+    return 1 if x_periodic and int(nx) <= 64 else (int(nx) + 59) // 60
+
+
 def batch_key(batch) -> str:
-    """Device, precision, form and, per width class, the box count and the
-    median height rounded to 16 rows."""
+    """Library revision, device, precision, form and, per width class, the box
+    count, the median height rounded to 16 rows and the number of strips."""
     import torch
+
+    from . import rsst_version
 
     dev = torch.cuda.get_device_name(torch.cuda.current_device())
     parts = []
     for c in range(4):
-        hs = sorted(int(s[1]) for s in batch.shapes if width_class(s[2]) == c)
-        if hs:
-            parts.append(f"w{c}:{len(hs)}x{16 * round(hs[len(hs) // 2] / 16)}")
+        boxes = [(int(s[1]), row_strips(s[2], _x_periodic(cfg))) for s, cfg in zip(batch.shapes, batch.cfgs)
+                 if width_class(s[2]) == c]
+        if boxes:
+            hs = sorted(h for h, _ in boxes)
+            parts.append(f"w{c}:{len(hs)}x{16 * round(hs[len(hs) // 2] / 16)}s{sum(n for _, n in boxes)}")
     form = batch.cfgs[0].get("form", "pvs")
-    return f"{dev}|{batch.prec}|{form}|" + ",".join(parts)
+    return f"{rsst_version()}|{dev}|{batch.prec}|{form}|" + ",".join(parts)
+
+
+def _x_periodic(cfg) -> bool:
+    bc = list(cfg.get("bc_lo", [])) + ["periodic"]
+    return bc[0] in ("periodic", 0)
 
 
 def _load(path):
