@@ -37,6 +37,7 @@
 #ifndef RSST_H
 #define RSST_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -143,6 +144,19 @@ typedef struct rsst_solver* rsst_handle;
  * after this call. */
 int rsst_init(const rsst_config* cfg, void* stream, rsst_handle* out);
 
+/* The size of the workspace that rsst_init would allocate for cfg (on the
+ * host, no device call; RSST_E_ARG or RSST_E_UNSUPPORTED where it would
+ * refuse cfg). */
+int rsst_workspace_bytes(const rsst_config* cfg, size_t* bytes);
+
+/* rsst_init in memory of the caller's, for callers with an allocator of their
+ * own (the differentiable rollout, which makes a handle per gradient, takes it
+ * from torch's): work, a device pointer on the current device, 256-byte
+ * aligned, of at least rsst_workspace_bytes(cfg) bytes (else RSST_E_ARG), whose
+ * earlier uses are complete or ordered before `stream`.  It belongs to the
+ * handle until rsst_destroy has returned, which leaves it allocated. */
+int rsst_init_in(const rsst_config* cfg, void* work, size_t bytes, void* stream, rsst_handle* out);
+
 /* Sets t = t0 and records, on the device, the maxima of c_tot over U from
  * which the next CFL step forms its dt.  rsst_step calls this by itself (t
  * unchanged) on the first CFL step; call it again after writing U from
@@ -218,7 +232,8 @@ int rsst_diag(rsst_handle h, const void* U, double out[8], void* stream);
  * and returns RSST_E_NONPHYSICAL if any was set. */
 int rsst_poll(rsst_handle h, uint32_t* flags);
 
-/* Frees the workspace.  The caller's arrays are untouched. */
+/* Synchronises the handle's device, then frees the workspace (rsst_init) or
+ * leaves it to the caller (rsst_init_in).  The caller's arrays are untouched. */
 int rsst_destroy(rsst_handle h);
 
 /* ---- One step that allocates nothing --------------------------------------

@@ -99,7 +99,7 @@ def lib():
                      "rsst_diag", "rsst_poll", "rsst_destroy", "rsst_batch_init", "rsst_batch_set_tiles",
                      "rsst_batch_get_tiles", "rsst_batch_run", "rsst_batch_times", "rsst_batch_poll",
                      "rsst_batch_destroy", "rsst_batch_plan", "rsst_adjoint_step", "rsst_adjoint_step_u1",
-                     "rsst_step_out", "rsst_adjoint_run", "rsst_steps_out"):
+                     "rsst_step_out", "rsst_adjoint_run", "rsst_steps_out", "rsst_workspace_bytes", "rsst_init_in"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -172,6 +172,20 @@ def make_config(cfg: dict, prec: str = "fp64", bg=None, bg_axis: int = -1,
 def rsst_init(cfg: rsst_config, stream=None) -> ctypes.c_void_p:
     h = ctypes.c_void_p()
     _check(lib().rsst_init(ctypes.byref(cfg), _stream(stream), ctypes.byref(h)), "rsst_init")
+    return h
+
+
+def rsst_workspace_bytes(cfg: rsst_config) -> int:
+    n = ctypes.c_size_t()
+    _check(lib().rsst_workspace_bytes(ctypes.byref(cfg), ctypes.byref(n)), "rsst_workspace_bytes")
+    return n.value
+
+
+def rsst_init_in(cfg: rsst_config, work, stream=None) -> ctypes.c_void_p:
+    """rsst_init in the device tensor `work` (uint8), which outlives the handle."""
+    h = ctypes.c_void_p()
+    _check(lib().rsst_init_in(ctypes.byref(cfg), _ptr(work), ctypes.c_size_t(work.numel() * work.element_size()),
+                              _stream(stream), ctypes.byref(h)), "rsst_init_in")
     return h
 
 
@@ -277,15 +291,25 @@ def rsst_version() -> str:
 class Solver:
     """Owns one rsst handle.  U is a contiguous CUDA tensor [nvar, ...]
     (float64, or float32 perturbation with prec='fp32_pert' and a float64
-    background tensor bg [nvar, nbg])."""
+    background tensor bg [nvar, nbg]).  torch_workspace: the largest workspace,
+    in bytes, to take from torch's allocator instead of a device allocation;
+    then every call has to be ordered after torch's current stream."""
+
+    h = None
 
     def __init__(self, cfg: dict, prec: str = "fp64", bg=None, bg_axis: int = -1,
-                 t_end: float = 0.0, stream=None, adjoint: bool = False):
+                 t_end: float = 0.0, stream=None, adjoint: bool = False, torch_workspace: int = 0):
         self.cfg = dict(cfg)
         self.prec = prec
         self._bg = bg  # keep the background alive as long as the handle
         self._c = make_config(cfg, prec, bg, bg_axis, t_end, adjoint)
-        self.h = rsst_init(self._c, stream)
+        self._work = None
+        if torch_workspace:
+            n = rsst_workspace_bytes(self._c)
+            if n <= torch_workspace:
+                import torch
+                self._work = torch.empty(n, dtype=torch.uint8, device="cuda")
+        self.h = rsst_init(self._c, stream) if self._work is None else rsst_init_in(self._c, self._work, stream)
 
     def prime(self, U, t0=0.0, stream=None):
         rsst_prime(self.h, U, t0, stream)
@@ -335,6 +359,7 @@ class Solver:
         if self.h is not None:
             rsst_destroy(self.h)
             self.h = None
+            self._work = None
 
     def __del__(self):
         try:

@@ -10,7 +10,6 @@
 #include <cstdint>
 #include <cstring>
 #include <atomic>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -28,8 +27,8 @@ struct rsst_solver {
   int nv;
   long long ncell;
   size_t elem;       // bytes per stored value
-  void* block;       // the workspace, owned; the next six lie in it
-  size_t block_bytes;
+  void* block;       // the workspace; the next six lie in it
+  bool owned;        // allocated here (else the caller's)
   void* u1;          // stage buffer
   double* scal;      // device scalars
   double* blkmax;    // per-workgroup maxima of c_tot of the current state; 2D: then as many for the
@@ -40,76 +39,6 @@ struct rsst_solver {
   bool primed;
   double* adj_work;  // adjoint workspace (flags & RSST_WITH_ADJOINT), or null
 };
-
-// ---- workspace blocks -------------------------------------------------------
-// A program that makes a solver per gradient (the rollout does) would pay for
-// device allocations and their release each time: 0.37 and 0.12 ms of the 2.0
-// ms of a 256^2 gradient over 40 steps; 0.03 ms and nothing with a kept block.  Up to
-// kKeepBlocks released blocks, kKeepBytes together, are kept for the next
-// solver of about that size on the same device; the oldest is freed where they
-// would not fit, and all of a device's where an allocation fails.  A block is
-// released after a device synchronisation, so nothing on any stream still uses
-// it, and the table is under a lock.
-struct KeptBlock {
-  void* p;
-  size_t bytes;
-  int device;
-};
-static constexpr int kKeepBlocks = 8;
-static constexpr size_t kKeepBytes = (size_t)64 << 20;
-static std::mutex g_keep_lock;
-static KeptBlock g_kept[kKeepBlocks];  // oldest first
-static int g_nkept = 0;
-
-static KeptBlock drop_kept(int i) {
-  const KeptBlock b = g_kept[i];
-  for (int q = i + 1; q < g_nkept; ++q) g_kept[q - 1] = g_kept[q];
-  --g_nkept;
-  return b;
-}
-
-// A block of at least n bytes on the current device (`dev`).
-static hipError_t take_block(int dev, size_t n, void** p, size_t* bytes) {
-  std::lock_guard<std::mutex> lock(g_keep_lock);
-  int best = -1;
-  for (int i = 0; i < g_nkept; ++i)
-    if (g_kept[i].device == dev && g_kept[i].bytes >= n && g_kept[i].bytes / 2 <= n &&
-        (best < 0 || g_kept[i].bytes < g_kept[best].bytes))
-      best = i;
-  if (best >= 0) {
-    const KeptBlock b = drop_kept(best);
-    *p = b.p;
-    *bytes = b.bytes;
-    return hipSuccess;
-  }
-  *bytes = n;
-  hipError_t e = hipMalloc(p, n);
-  if (e == hipSuccess) return e;
-  (void)hipGetLastError();
-  bool freed = false;
-  for (int i = g_nkept - 1; i >= 0; --i)
-    if (g_kept[i].device == dev) {
-      (void)hipFree(drop_kept(i).p);
-      freed = true;
-    }
-  return freed ? hipMalloc(p, n) : e;
-}
-
-static void release_block(int dev, void* p, size_t bytes) {
-  if (!p) return;
-  std::lock_guard<std::mutex> lock(g_keep_lock);
-  if (bytes > kKeepBytes) {
-    (void)hipFree(p);
-    return;
-  }
-  size_t sum = bytes;
-  for (int i = 0; i < g_nkept; ++i) sum += g_kept[i].bytes;
-  while (g_nkept > 0 && (g_nkept == kKeepBlocks || sum > kKeepBytes)) {
-    sum -= g_kept[0].bytes;
-    (void)hipFree(drop_kept(0).p);
-  }
-  g_kept[g_nkept++] = KeptBlock{p, bytes, dev};
-}
 
 static int check(hipError_t e) { return e == hipSuccess ? RSST_OK : RSST_E_DEVICE; }
 
@@ -275,6 +204,33 @@ __global__ void __launch_bounds__(64) noalloc_flags_kernel(const double* scal, u
 
 static size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// A solver's workspace, one block: the offsets of its parts, its maxima (2D:
+// two sets, see rsst_solver) and its size.
+struct Workspace {
+  size_t u1, scal, blk, part, diag, adj;
+  size_t nmax, bytes;
+};
+
+static Workspace workspace_of(const rsst_config& c, const Geometry& g) {
+  const long long ncell = (long long)c.n[0] * c.n[1] * c.n[2];
+  const size_t elem = c.prec == RSST_FP32_PERT ? sizeof(float) : sizeof(double);
+  Workspace w{};
+  auto part_of = [&w](size_t bytes) {
+    const size_t o = w.bytes;
+    w.bytes += round256(bytes);
+    return o;
+  };
+  w.nmax = (size_t)g.nslot * (c.ndim == 2 ? 2 : 1);
+  w.u1 = part_of((size_t)(c.ndim + 2) * ncell * elem);
+  w.scal = part_of(rsstk::kNumScalars * sizeof(double));
+  w.blk = part_of(w.nmax * sizeof(double));
+  w.part = part_of((size_t)rsstk::diag_partials(ncell) * 8 * sizeof(double));
+  w.diag = part_of(8 * sizeof(double));
+  if (c.flags & RSST_WITH_ADJOINT)
+    w.adj = part_of(rsstk::adjoint_workspace_doubles(c.ndim, c.n, ncell) * sizeof(double));
+  return w;
+}
+
 extern "C" {
 
 const char* rsst_strerror(int s) {
@@ -292,56 +248,52 @@ const char* rsst_strerror(int s) {
 
 const char* rsst_version(void) { return "rsst-gfx950 stage-v21"; }
 
-int rsst_init(const rsst_config* cfg, void* stream, rsst_handle* out) {
-  if (!out) return RSST_E_ARG;
+int rsst_workspace_bytes(const rsst_config* cfg, size_t* bytes) {
+  if (!bytes) return RSST_E_ARG;
+  const int st = validate(cfg);
+  if (st != RSST_OK) return st;
+  *bytes = workspace_of(*cfg, rsstk::plan_geometry(cfg->ndim, cfg->n, cfg->bc_lo[0] == RSST_PERIODIC)).bytes;
+  return RSST_OK;
+}
+
+// A handle in `work` (of the caller, `bytes` long), or in memory allocated here
+// where that is null.
+static int init_in(const rsst_config* cfg, void* work, size_t bytes, void* stream, rsst_handle* out) {
   *out = nullptr;
-  int st = validate(cfg);
+  const int st = validate(cfg);
   if (st != RSST_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-
   rsst_solver* h = new (std::nothrow) rsst_solver();
   if (!h) return RSST_E_NOMEM;
   h->cfg = *cfg;
   h->nv = cfg->ndim + 2;
   h->ncell = (long long)cfg->n[0] * cfg->n[1] * cfg->n[2];
   h->elem = cfg->prec == RSST_FP32_PERT ? sizeof(float) : sizeof(double);
-  if (hipGetDevice(&h->device) != hipSuccess) { delete h; return RSST_E_DEVICE; }
-
   StageArgs& a = h->args;
   fill_args(cfg, h->ncell, a);
   h->npart = rsstk::diag_partials(h->ncell);
-  // one block: U1, scalars, maxima, diagnostics, adjoint workspace
-  const size_t nscal = rsstk::kNumScalars;
-  const size_t nmax = (size_t)a.nslot * (cfg->ndim == 2 ? 2 : 1);
-  const bool adjoint = (cfg->flags & RSST_WITH_ADJOINT) != 0;
-  size_t at = 0;
-  auto part_of = [&at](size_t bytes) {
-    const size_t o = at;
-    at += round256(bytes);
-    return o;
-  };
-  const size_t o_u1 = part_of((size_t)h->nv * h->ncell * h->elem), o_scal = part_of(nscal * sizeof(double));
-  const size_t o_blk = part_of(nmax * sizeof(double)), o_part = part_of((size_t)h->npart * 8 * sizeof(double));
-  const size_t o_diag = part_of(8 * sizeof(double));
-  const size_t o_adj =
-      adjoint ? part_of(rsstk::adjoint_workspace_doubles(cfg->ndim, cfg->n, h->ncell) * sizeof(double)) : 0;
-  if (take_block(h->device, at, &h->block, &h->block_bytes) != hipSuccess) {
+  const Workspace w = workspace_of(*cfg, a.geo);
+  if (work && (((uintptr_t)work & 255) || bytes < w.bytes)) { delete h; return RSST_E_ARG; }
+  if (hipGetDevice(&h->device) != hipSuccess) { delete h; return RSST_E_DEVICE; }
+  h->block = work;
+  h->owned = !work;
+  if (h->owned && hipMalloc(&h->block, w.bytes) != hipSuccess) {
     (void)hipGetLastError();
     delete h;
     return RSST_E_NOMEM;
   }
   char* const base = (char*)h->block;
-  h->u1 = base + o_u1;
-  h->scal = (double*)(base + o_scal);
-  h->blkmax = (double*)(base + o_blk);
-  h->part = (double*)(base + o_part);
-  h->diag_out = (double*)(base + o_diag);
-  h->adj_work = adjoint ? (double*)(base + o_adj) : nullptr;
+  h->u1 = base + w.u1;
+  h->scal = (double*)(base + w.scal);
+  h->blkmax = (double*)(base + w.blk);
+  h->part = (double*)(base + w.part);
+  h->diag_out = (double*)(base + w.diag);
+  h->adj_work = cfg->flags & RSST_WITH_ADJOINT ? (double*)(base + w.adj) : nullptr;
   // zeroed before any launch on any stream
   const size_t adj_z = h->adj_work ? rsstk::adjoint_zeroed_offset(cfg->ndim, cfg->n, h->ncell) : 0;
   const size_t adj_n = h->adj_work ? rsstk::adjoint_workspace_doubles(cfg->ndim, cfg->n, h->ncell) : 0;
-  if (hipMemsetAsync(h->scal, 0, nscal * sizeof(double), s) != hipSuccess ||
-      hipMemsetAsync(h->blkmax, 0, nmax * sizeof(double), s) != hipSuccess ||
+  if (hipMemsetAsync(h->scal, 0, rsstk::kNumScalars * sizeof(double), s) != hipSuccess ||
+      hipMemsetAsync(h->blkmax, 0, w.nmax * sizeof(double), s) != hipSuccess ||
       (adj_n > adj_z && hipMemsetAsync(h->adj_work + adj_z, 0, (adj_n - adj_z) * sizeof(double), s) != hipSuccess) ||
       hipStreamSynchronize(s) != hipSuccess) {
     rsst_destroy(h);
@@ -351,6 +303,16 @@ int rsst_init(const rsst_config* cfg, void* stream, rsst_handle* out) {
   h->primed = false;
   *out = h;
   return RSST_OK;
+}
+
+int rsst_init(const rsst_config* cfg, void* stream, rsst_handle* out) {
+  return out ? init_in(cfg, nullptr, 0, stream, out) : RSST_E_ARG;
+}
+
+int rsst_init_in(const rsst_config* cfg, void* work, size_t bytes, void* stream, rsst_handle* out) {
+  if (!out) return RSST_E_ARG;
+  *out = nullptr;
+  return work ? init_in(cfg, work, bytes, stream, out) : RSST_E_ARG;
 }
 
 int rsst_prime(rsst_handle h, const void* U, double t0, void* stream) {
@@ -569,9 +531,8 @@ int rsst_destroy(rsst_handle h) {
   int dev = h->device;
   (void)hipGetDevice(&dev);
   if (dev != h->device) (void)hipSetDevice(h->device);
-  const bool idle = hipDeviceSynchronize() == hipSuccess;
-  if (idle) release_block(h->device, h->block, h->block_bytes);
-  else (void)hipFree(h->block);  // not known to be out of use: never kept
+  (void)hipDeviceSynchronize();
+  if (h->owned) (void)hipFree(h->block);
   if (dev != h->device) (void)hipSetDevice(dev);
   delete h;
   return RSST_OK;

@@ -30,6 +30,13 @@ import torch
 
 from . import Solver
 
+# A rollout makes a solver of its own.  Workspaces of up to 64 MiB come from
+# torch's allocator, which keeps them for the next one and gives them back as it
+# does its tensors: making and closing the solver of a 256^2 gradient takes 24 us
+# so and 47 with a device allocation.  Larger ones are allocated and freed each
+# time, so that memory kept by torch does not turn "auto" below to checkpoints.
+TORCH_WORKSPACE = 64 << 20
+
 
 class RSSTRollout(torch.autograd.Function):
     @staticmethod
@@ -40,7 +47,7 @@ class RSSTRollout(torch.autograd.Function):
         K = trajectory_or_interval(U0, nsteps, checkpoint_every)
         c = dict(cfg)
         c["xi"] = float(xi)
-        solver = Solver(c, adjoint=True)
+        solver = Solver(c, adjoint=True, torch_workspace=TORCH_WORKSPACE)
         ctx.solver, ctx.nsteps, ctx.dt, ctx.K = solver, nsteps, float(dt), K
         ctx.use_graph = bool(use_graph)
         ctx.xi_needs_grad = isinstance(xi, torch.Tensor) and xi.requires_grad
