@@ -149,6 +149,19 @@ int rsst_init(const rsst_config* cfg, void* stream, rsst_handle* out);
  * refuse cfg). */
 int rsst_workspace_bytes(const rsst_config* cfg, size_t* bytes);
 
+/* The launch plan of cfg (on the host, no device call; refuses what rsst_init
+ * refuses), for logs and tests.  Results do not depend on it. */
+enum rsst_plan_field {
+  RSST_PLAN_CHUNK = 0,   /* rows (2D) or planes (3D) per march               */
+  RSST_PLAN_BLOCKS = 1,  /* workgroups of a stage                            */
+  RSST_PLAN_WAVES = 2,   /* waves of each                                    */
+  RSST_PLAN_ROWS = 3,    /* 2D: 1 whole rows, 0 strips                       */
+  RSST_PLAN_STEP = 4,    /* 2D: workgroups of a step in one launch, 0: runs
+                            take the stages one by one                       */
+  RSST_PLAN_FIELDS = 5
+};
+int rsst_plan(const rsst_config* cfg, int plan[RSST_PLAN_FIELDS]);
+
 /* rsst_init in memory of the caller's, for callers with an allocator of their
  * own (the differentiable rollout, which makes a handle per gradient, takes it
  * from torch's): work, a device pointer on the current device, 256-byte

@@ -99,7 +99,8 @@ def lib():
                      "rsst_diag", "rsst_poll", "rsst_destroy", "rsst_batch_init", "rsst_batch_set_tiles",
                      "rsst_batch_get_tiles", "rsst_batch_run", "rsst_batch_times", "rsst_batch_poll",
                      "rsst_batch_destroy", "rsst_batch_plan", "rsst_adjoint_step", "rsst_adjoint_step_u1",
-                     "rsst_step_out", "rsst_adjoint_run", "rsst_steps_out", "rsst_workspace_bytes", "rsst_init_in"):
+                     "rsst_step_out", "rsst_adjoint_run", "rsst_steps_out", "rsst_workspace_bytes", "rsst_init_in",
+                     "rsst_plan"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -179,6 +180,16 @@ def rsst_workspace_bytes(cfg: rsst_config) -> int:
     n = ctypes.c_size_t()
     _check(lib().rsst_workspace_bytes(ctypes.byref(cfg), ctypes.byref(n)), "rsst_workspace_bytes")
     return n.value
+
+
+PLAN_FIELDS = ("chunk", "blocks", "waves", "rows", "step")
+
+
+def rsst_plan(cfg: rsst_config) -> dict:
+    """The launch plan of cfg (host only): see rsst_plan_field in rsst.h."""
+    a = (ctypes.c_int * len(PLAN_FIELDS))()
+    _check(lib().rsst_plan(ctypes.byref(cfg), a), "rsst_plan")
+    return dict(zip(PLAN_FIELDS, a))
 
 
 def rsst_init_in(cfg: rsst_config, work, stream=None) -> ctypes.c_void_p:

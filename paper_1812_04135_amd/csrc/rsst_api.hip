@@ -256,6 +256,19 @@ int rsst_workspace_bytes(const rsst_config* cfg, size_t* bytes) {
   return RSST_OK;
 }
 
+int rsst_plan(const rsst_config* cfg, int plan[RSST_PLAN_FIELDS]) {
+  if (!plan) return RSST_E_ARG;
+  const int st = validate(cfg);
+  if (st != RSST_OK) return st;
+  const Geometry g = rsstk::plan_geometry(cfg->ndim, cfg->n, cfg->bc_lo[0] == RSST_PERIODIC);
+  plan[RSST_PLAN_CHUNK] = g.km;
+  plan[RSST_PLAN_BLOCKS] = g.nblk;
+  plan[RSST_PLAN_WAVES] = g.threads / 64;
+  plan[RSST_PLAN_ROWS] = g.rows;
+  plan[RSST_PLAN_STEP] = g.fused ? g.nblkF : 0;
+  return RSST_OK;
+}
+
 // A handle in `work` (of the caller, `bytes` long), or in memory allocated here
 // where that is null.
 static int init_in(const rsst_config* cfg, void* work, size_t bytes, void* stream, rsst_handle* out) {

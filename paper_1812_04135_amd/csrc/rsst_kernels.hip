@@ -278,16 +278,21 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
   }
   G.ntile_s = (G.ns + G.ts - 1) / G.ts;
   if (ndim == 3) {
-    // One workgroup fills a CU, so the grid runs in rounds of 256 workgroups,
-    // each as long as its chunk of km planes plus about 0.7 plane of start-up
-    // (a chunk re-reads 4 planes and forms one extra face): the cheapest km.
+    // A CU holds eight waves (two per SIMD), one full tile or several of a grid
+    // with fewer rows than a tile (two of up to four waves, four of two), so the
+    // grid runs in rounds of that many workgroups per CU, each as long as its
+    // chunk of km planes plus about 0.7 plane of start-up (a chunk re-reads 4
+    // planes and forms one extra face): the cheapest km.
     // (Halving 128 planes until there were 256 workgroups left 187 x 141 x 230
     // at 288, two rounds of 32 planes where one of 33 does: FP32 1.04 ms per
-    // step, 0.55 with it.)
+    // step, 0.55 with it.  One workgroup per CU whatever its size left SIMDs
+    // empty: 8 x 8 x 2000 FP64 83 us with chunks of 8, 66 with 4; 64 x 4 x 2000
+    // 76 with 8, 45 with 2; halved until 256 workgroups, 66 and 61 with 4.)
+    const int per_cu = 8 / (G.nwx * G.ts / 2);
     int km = 1;
     double best = 1e300;
     for (int q = 1; q <= 128 && q <= G.nm; ++q) {
-      const long long rounds = ((long long)G.ntile_s * ((G.nm + q - 1) / q) + 255) / 256;
+      const long long round = 256ll * per_cu, rounds = ((long long)G.ntile_s * ((G.nm + q - 1) / q) + round - 1) / round;
       const double c = (double)rounds * (q + 0.7);
       if (c < best) { best = c; km = q; }
     }
