@@ -379,21 +379,24 @@ static int prime_once(rsst_handle h, const void* U, double dt_fixed, hipStream_t
 // A 2D step in one launch, from uin to uout (another array), U1 to u1out
 // unless null.  A CFL step reads the maxima and t in every workgroup, so it
 // leaves the new ones in the other buffers: such steps come in pairs, half 0
-// and half 1, after which they are back in their own.
-static hipError_t step2d(rsst_handle h, int half, const void* uin, void* u1out, void* uout, double dt_fixed,
-                         hipStream_t s) {
+// and half 1, after which they are back in their own.  after: it follows another
+// such step, whose maxima are the first nblkF (at most 256, so no barrier is
+// needed for them; the slots of the largest launch may be thousands).
+static hipError_t step2d(rsst_handle h, int half, bool after, const void* uin, void* u1out, void* uout,
+                         double dt_fixed, hipStream_t s) {
   StageArgs a = h->args;
   a.dt_fixed = dt_fixed > 0.0 ? dt_fixed : 0.0;
   a.uin = a.un = uin;
   a.u1out = u1out;
   a.uout = uout;
   if (!(dt_fixed > 0.0)) {
-    double* const blk[2] = {h->blkmax, h->blkmax + a.nslot};
+    double* const blk[2] = {h->blkmax, h->blkmax + a.geo.nslot};
     double* const t[2] = {h->scal + rsstk::kTime, h->scal + rsstk::kTimeAlt};
     a.blkmax = blk[half];
     a.blkmax_out = blk[1 - half];
     a.t_in = t[half];
     a.t_out = t[1 - half];
+    if (after) a.nslot = a.geo.nblkF;
   }
   return h->elem == sizeof(float) ? rsstk::launch_step2d<float>(a, s) : rsstk::launch_step2d<double>(a, s);
 }
@@ -423,7 +426,7 @@ int rsst_step_out(rsst_handle h, const void* U, void* U1, void* Unext, double dt
   int st = prime_once(h, U, dt_fixed, s);
   if (st != RSST_OK) return st;
   // in one launch where that leaves the maxima and t in place
-  const hipError_t e = h->args.geo.fused && dt_fixed > 0.0 ? step2d(h, 0, U, U1, Unext, dt_fixed, s)
+  const hipError_t e = h->args.geo.fused && dt_fixed > 0.0 ? step2d(h, 0, false, U, U1, Unext, dt_fixed, s)
                                                            : step_split(h, U, U1, Unext, dt_fixed, s);
   if (e != hipSuccess) return RSST_E_DEVICE;
   h->primed = true;
@@ -435,6 +438,7 @@ int rsst_steps_out(rsst_handle h, void* const* U_list, void* const* U1_list, int
   if (!h || !U_list || !U1_list || nsteps < 0 || !std::isfinite(dt_fixed)) return RSST_E_ARG;
   for (int n = 0; n < nsteps; ++n)
     if (!U_list[n] || !U1_list[n] || !U_list[n + 1]) return RSST_E_ARG;
+  bool after = false;  // the launch before was a step in one launch
   for (int n = 0; n < nsteps; ++n) {
     void* const* u = U_list + n;
     if (h->args.geo.fused && !(dt_fixed > 0.0) && n + 1 < nsteps && distinct(u[0], U1_list[n], u[1]) &&
@@ -443,13 +447,14 @@ int rsst_steps_out(rsst_handle h, void* const* U_list, void* const* U1_list, int
       hipStream_t s = (hipStream_t)stream;
       const int st = prime_once(h, u[0], dt_fixed, s);
       if (st != RSST_OK) return st;
-      if (step2d(h, 0, u[0], U1_list[n], u[1], dt_fixed, s) != hipSuccess ||
-          step2d(h, 1, u[1], U1_list[n + 1], u[2], dt_fixed, s) != hipSuccess)
+      if (step2d(h, 0, after, u[0], U1_list[n], u[1], dt_fixed, s) != hipSuccess ||
+          step2d(h, 1, true, u[1], U1_list[n + 1], u[2], dt_fixed, s) != hipSuccess)
         return RSST_E_DEVICE;
-      h->primed = true;
+      h->primed = after = true;
       ++n;
       continue;
     }
+    after = false;
     const int st = rsst_step_out(h, u[0], U1_list[n], u[1], dt_fixed, stream);
     if (st != RSST_OK) return st;
   }
@@ -486,8 +491,8 @@ int rsst_steps(rsst_handle h, void* U, int nsteps, double dt_fixed, void* stream
     const int st = prime_once(h, U, dt_fixed, s);
     if (st != RSST_OK) return st;
     for (; q + 1 < nsteps; q += 2)
-      if (step2d(h, 0, U, nullptr, h->u1, dt_fixed, s) != hipSuccess ||
-          step2d(h, 1, h->u1, nullptr, U, dt_fixed, s) != hipSuccess)
+      if (step2d(h, 0, q > 0, U, nullptr, h->u1, dt_fixed, s) != hipSuccess ||
+          step2d(h, 1, true, h->u1, nullptr, U, dt_fixed, s) != hipSuccess)
         return RSST_E_DEVICE;
     h->primed = true;
   }
@@ -629,7 +634,7 @@ int rsst_step_noalloc(const rsst_config* cfg, void* U, double dt_fixed, uint32_t
   const size_t elem = cfg->prec == RSST_FP32_PERT ? sizeof(float) : sizeof(double);
   StageArgs a;
   fill_args(cfg, ncell, a);
-  a.nslot = a.geo.nblk;  // one stage per launch
+  a.nslot = a.geo.nslot = a.geo.nblk;  // one stage per launch
   // scratch layout: scalars | CFL maxima | U1, each 256-byte aligned
   const size_t o_blk = round256(rsstk::kNumScalars * sizeof(double));
   const size_t o_u1 = o_blk + round256((size_t)a.nslot * sizeof(double));

@@ -37,6 +37,7 @@
 //     velocity) is computed once, by the cell that owns it;
 //   * workgroup ids are remapped so that consecutive tiles (which share
 //     halo rows) run on the same XCD and share its L2.
+#include <algorithm>
 #include <cstdlib>
 
 #include "rsst_row2.h"
@@ -200,6 +201,40 @@ static int chunk_override(int km) {
   return km;
 }
 
+// About the us of a stage by whole-row workgroups of chunks of q rows (less some
+// 4 of launch and first loads): a row takes a wave alone on its SIMD 1.4 (rows
+// of several waves, which wait for each other, 1.5), two waves 2.4, each further
+// one 0.9 (1.0); four fit a SIMD, and a chunk starts with the time of 1.5 (0.5)
+// rows.  Fitted to 128 grids of 1000 to 131072 wave-rows, rows of 1, 2, 3, 4 and
+// 8 waves, both storage types: the chunk it picks is within 1% of the best
+// measured on average, 6 to 11% off at the worst.
+static double rows_cost(int nwx, int nm, int q) {
+  const int per = 16 / nwx, p = ((nm + q - 1) / q + 255) / 256;  // workgroups a CU holds, and gets
+  const double one = nwx == 1 ? 1.4 : 1.5, more = nwx == 1 ? 0.9 : 1.0, start = nwx == 1 ? 1.5 : 0.5;
+  auto row = [&](int wg) {
+    const double w = wg * nwx / 4.0;
+    return wg == 0 ? 0.0 : (w <= 1.0 ? one : 2.4 + (w - 2.0) * more);
+  };
+  return (q + start) * ((p / per) * row(per) + row(p % per));
+}
+
+// The chunk of the least rows_cost (left in `cost`).  At most 35 rows, or what
+// makes one round of all workgroups (more of them read more maxima, each all of
+// them: 64 x 10^6 FP64 4.4 ms per step with 24 rows, 2.6 with 257).  From 8 rows
+// on odd ones only: chunks whose first rows are a power of two apart meet in the
+// same memory channels (128 x 65536 FP64 403 us with 16 rows, 379 with 32, 323
+// with 33).
+static int rows_chunk(int nwx, int nm, double& cost) {
+  const int full = 256 * (16 / nwx), top = std::max(35, (nm + full - 1) / full | 1);
+  int km = 1;
+  cost = 1e300;
+  for (int q = 1; q <= top && q <= nm; q += q < 7 ? 1 : 2) {
+    const double c = rows_cost(nwx, nm, q);
+    if (c < cost) { cost = c; km = q; }
+  }
+  return km;
+}
+
 Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
   Geometry G{};
   G.ndim = ndim;
@@ -226,17 +261,27 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
       if (c < best) { best = c; km = q; }
     }
     // Whole rows instead (a workgroup of nwx waves holds a row, three barriers
-    // per row) where strips would need more waves and the grid has at most
-    // four waves per SIMD: the step is then mostly latency, and the strips'
-    // extra waves sit on some SIMDs only (us per step: 256^2 12.6, with strips
-    // 14.1; 512^2 21.2 and 23.1; but 1024^2 62 and 50, 389 x 301 25 and 17.6;
-    // since dt is formed behind the first loads 256^2 takes 11.2, 512^2 19.4).
-    // Two rows per iteration where that still gives every SIMD two waves.
-    G.rows = G.cols.ncol > G.nwx && (long long)G.nwx * G.nm <= 4096 && G.nwx <= 8;
-    if (G.rows) {
-      G.np = (long long)((G.nm + 1) / 2) * G.nwx >= 2048 ? 2 : 1;
-      km = 64;
-      while (km > G.np && (G.nm + km - 1) / km < 512) km >>= 1;
+    // per row) where strips would need more waves for it.  Up to four waves per
+    // SIMD a step is mostly latency and whole rows are faster (us per step,
+    // rows and strips: 256 x 256 10.7 and 13.1, 256 x 1000 18.8 and 20.9, 512 x
+    // 512 18.5 and 21.2, 192 x 341 13.0 and 13.2), but rows of five to seven
+    // waves only while a CU has one (384 x 256 12.6 and 13.6, 384 x 341 18.1 and
+    // 16.2).  On larger grids rows of one, two and four waves, which fill the
+    // SIMDs, and of three on the largest, by what either costs: strips 1.04 us
+    // per row and SIMD, of whose lanes they waste a fifth to a half there (64
+    // cells between walls: 64 x 8000 FP64 35 and 40, 64 x 65536 165 and 240; 128
+    // x 30000 139 and 178; 256 x 16384 151 and 172, but 256 x 1100 24.5 and 21.2;
+    // 192 x 20000 150 and 160, but 192 x 5000 48.7 and 47.9).  Rows of eight
+    // gain 5% there with FP64 and lose 6% with FP32 storage (512 x 16384), whose
+    // registers leave a CU one workgroup instead of two.
+    const long long waves = (long long)G.nwx * G.nm;
+    if (G.cols.ncol > G.nwx && G.nwx <= 8) {
+      double cost;
+      const int q = rows_chunk(G.nwx, G.nm, cost);
+      if (waves <= 4096) G.rows = G.nwx <= 4 || G.nwx == 8 || G.nm <= 256;
+      else G.rows = (G.nwx == 1 || G.nwx == 2 || G.nwx == 4 || (G.nwx == 3 && waves >= 32768)) &&
+                    cost < 0.2 + 1.04 * G.cols.ncol * (double)G.nm / 1024.0;
+      if (G.rows) km = q;
     }
     km = chunk_override(km);
     G.km = km < G.nm ? km : G.nm;
@@ -245,13 +290,12 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
     if (G.rows) {
       G.nblk = G.nchunk;
       G.threads = 64 * G.nwx;
-      G.lds_bytes = (size_t)carve2(1, G.nwx, G.np).total * sizeof(double);
+      G.lds_bytes = (size_t)carve2(1, G.nwx).total * sizeof(double);
     } else {
       G.nblk = (G.cols.ncol * G.nchunk + kWaves2 - 1) / kWaves2;
       G.threads = 64 * kWaves2;
       G.lds_bytes = (size_t)(kRed2 + kWaves2) * sizeof(double);
     }
-    G.colsF = plan_cols2(G.nx, x_per, 4);
     // Both stages in one launch: tiles of 4 r rows, one per CU (256) at a
     // time, each 4.4 us and 0.85 us per row of its SIMDs (r + 1 rows of stage
     // 1, r of stage 2): the smallest r that needs one round.  It saves a

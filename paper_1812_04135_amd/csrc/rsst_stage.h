@@ -286,7 +286,7 @@ __device__ __forceinline__ void cfl_epilogue(const StageArgs& A, double* red, do
     double m = 0.0;
     for (int q = 0; q < (int)(blockDim.x >> 6); ++q) m = fmax(m, red[q]);
     // slots past this launch's workgroups (another kernel's) hold 0
-    for (int q = blockIdx.x; q < A.nslot; q += gridDim.x) A.blkmax_out[q] = q == (int)blockIdx.x ? m : 0.0;
+    for (int q = blockIdx.x; q < A.geo.nslot; q += gridDim.x) A.blkmax_out[q] = q == (int)blockIdx.x ? m : 0.0;
     if (blockIdx.x == 0) *A.t_out = *A.t_in + dt;
   }
 }

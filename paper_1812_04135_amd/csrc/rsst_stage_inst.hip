@@ -103,18 +103,20 @@ __global__ void __launch_bounds__(64 * kWaves2) __attribute__((amdgpu_waves_per_
   if constexpr (STAGE == 2) cfl_epilogue(A, lds + kRed2, cmax, dt);
 }
 
-// 2D grids, one stage, a workgroup per whole row (rsst_row2.h): NP rows per
-// march iteration.
-template <int STAGE, typename ST, int FORM, int NP>
+// 2D grids, one stage, a workgroup per whole row (rsst_row2.h): up to 8 waves.
+// (16, for rows of 961 to 1024 cells, would hold every form to 128 VGPRs, which
+// some exceed: FP32 512 x 512 19.1 us per step instead of 18.1, 256 x 256 11.3
+// and 11.1; 1024 x 32768 FP64, 1222 instead of 1319, was the only gain.)
+template <int STAGE, typename ST, int FORM>
 __global__ void __launch_bounds__(512) row_kernel2d(const StageArgs A) {
   extern __shared__ double lds[];
-  double* red = lds + carve2(A.geo.ts, A.geo.nwx, NP).red;
+  double* red = lds + carve2(A.geo.ts, A.geo.nwx).red;
   StepDt<STAGE> sd{A, red, {}};
   sd.begin();
   unsigned bad = 0;
   double dt = 0.0;
-  const double cmax = stage_body2<STAGE, ST, FORM, NP>(A, lds, xcd_tile(blockIdx.x, A.geo.nblk),
-                                                       [&]() { return dt = sd.finish(); }, bad);
+  const double cmax = stage_body2<STAGE, ST, FORM>(A, lds, xcd_tile(blockIdx.x, A.geo.nblk),
+                                                   [&]() { return dt = sd.finish(); }, bad);
   if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
   if constexpr (STAGE == 2) cfl_epilogue(A, red, cmax, dt);
 }
@@ -162,16 +164,15 @@ static hipError_t launch_stage_k(const StageArgs& a, hipStream_t s) {
                     a, s);
 }
 
-template <int STAGE, typename ST, int FORM, int NP>
+template <int STAGE, typename ST, int FORM>
 static hipError_t launch_rows_2d(const StageArgs& a, hipStream_t s) {
   static int lds_set[64] = {0};
-  return launch_geo(row_kernel2d<STAGE, ST, FORM, NP>, lds_set, a.geo.nblk, a.geo.threads, a.geo.lds_bytes, a, s);
+  return launch_geo(row_kernel2d<STAGE, ST, FORM>, lds_set, a.geo.nblk, a.geo.threads, a.geo.lds_bytes, a, s);
 }
 
 template <int STAGE, typename ST, int FORM>
 static hipError_t launch_stage_2d(const StageArgs& a, hipStream_t s) {
-  if (a.geo.rows)
-    return a.geo.np == 2 ? launch_rows_2d<STAGE, ST, FORM, 2>(a, s) : launch_rows_2d<STAGE, ST, FORM, 1>(a, s);
+  if (a.geo.rows) return launch_rows_2d<STAGE, ST, FORM>(a, s);
   static int lds_set[64] = {0};
   return launch_geo(stage_kernel2d<STAGE, ST, FORM>, lds_set, a.geo.nblk, a.geo.threads, a.geo.lds_bytes, a, s);
 }

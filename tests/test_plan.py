@@ -39,3 +39,35 @@ def test_3d_tiles_fill_the_cus(nx, ns, waves, per_cu, nz):
     assert p["blocks"] <= CUS * per_cu * max(1, -(-tiles * -(-nz // 128) // (CUS * per_cu)))
     if p["chunk"] >= 4:
         assert p["blocks"] >= 0.8 * CUS * per_cu
+
+
+# whole rows or strips: (grid, walls in x, rows)
+@pytest.mark.parametrize("n,bc,rows", [
+    ([64, 100], "periodic", 0), ([64, 100], "reflect", 1), ([60, 100], "reflect", 0), ([64, 4096], "reflect", 1), ([64, 4100], "reflect", 0), ([64, 65536], "reflect", 1),
+    ([64, 10 ** 6], "reflect", 1), ([128, 2048], "periodic", 1), ([128, 30000], "periodic", 1), ([120, 30000], "periodic", 0),
+    ([256, 1024], "periodic", 1), ([256, 1100], "periodic", 0), ([256, 16384], "periodic", 1), ([240, 16384], "periodic", 0),
+    ([192, 1365], "periodic", 1), ([192, 5000], "periodic", 0), ([192, 20000], "periodic", 1), ([320, 204], "periodic", 1), ([320, 400], "periodic", 0),
+    ([448, 256], "periodic", 1), ([448, 585], "periodic", 0), ([512, 512], "periodic", 1), ([512, 513], "periodic", 0),
+    ([512, 2000], "periodic", 0), ([512, 16384], "periodic", 0), ([1024, 16], "periodic", 0), ([1024, 3000], "periodic", 0),
+    ([1024, 32768], "periodic", 0), ([1000, 30000], "periodic", 0), ([700, 40000], "periodic", 0)])
+def test_2d_whole_rows_where_their_waves_are_full_and_even(n, bc, rows):
+    p = _plan(n, bc)
+    assert p["rows"] == rows
+    assert p["waves"] == (-(-n[0] // 64) if rows else 4)
+
+
+@pytest.mark.parametrize("nx", [64, 128, 192, 256, 512])
+@pytest.mark.parametrize("nm", [64, 1000, 4096, 20000, 65536, 262144, 10 ** 6])
+def test_2d_whole_row_chunks(nx, nm):
+    """At most about one round of all the workgroups that fit (each reads the
+    maxima of all), or 35 rows, and no chunk of a power of two of 8 rows or
+    more."""
+    if nx * nm * 32 >= 1 << 31:
+        pytest.skip("a 2D state of 2 GiB")
+    p = _plan([nx, nm], "reflect")
+    if not p["rows"]:
+        return
+    full = CUS * (16 // (nx // 64))
+    assert p["blocks"] == -(-nm // p["chunk"])
+    assert p["chunk"] <= max(35, -(-nm // full) + 1)
+    assert p["chunk"] < 8 or p["chunk"] % 2 == 1
