@@ -246,7 +246,7 @@ const char* rsst_strerror(int s) {
   }
 }
 
-const char* rsst_version(void) { return "rsst-gfx950 stage-v21"; }
+const char* rsst_version(void) { return "rsst-gfx950 stage-v22"; }
 
 int rsst_workspace_bytes(const rsst_config* cfg, size_t* bytes) {
   if (!bytes) return RSST_E_ARG;

@@ -50,7 +50,7 @@
 
 namespace rsstk {
 
-constexpr int kBatchThreads = 256;  // one box row: at most 4 waves
+constexpr int kBatchThreads = 256;  // four waves, each marching strips of its own rows
 // Persistent workgroups per CU.  A workgroup is one wave per SIMD, so this is
 // also the waves per SIMD the kernel is compiled for (its register budget).
 // 512 FP32 boxes, 20 steps, 16-row strips: 14.4 ms with three, 15.8 ms with
@@ -413,14 +413,35 @@ static int host_map_row(int q, int n, int refl_lo, int refl_hi) {
   return q;
 }
 
-// Strip blocks of one box and their dependency lists, appended to `items`.
-// A block is `groups` strips of `km` rows (the rows of one workgroup row
-// group); the march runs along y.
-static int plan_box(const rsst_config& c, const int strip[4], int b, std::vector<Item>& items, int& km,
+// Chunks of strip rows in a row block: as many as rows of the box's waves fill
+// the four of a workgroup.  Rows of 61 to 64 cells between walls are one wave
+// wide but two strips, so a wave marches two chunks of a block of four: in small
+// batches (`halve`) such a block is two chunks, one march per wave.  us per
+// step with four and two, 64 x 64 FP64: 1 box 77 and 44, 20 boxes 76 and 43, 384
+// boxes 123 and 108; 64 x 200: 200 boxes (800 blocks of four) 186 and 168, 384
+// boxes (1536) 320 and 326, 768 boxes 636 and 666.
+static int chunks_of(const rsst_config& c, bool halve) {
+  const int nwx = (c.n[0] + 63) / 64;
+  return halve && nwx == 1 && plan_cols2(c.n[0], c.bc_lo[0] == RSST_PERIODIC, 2).ncol == 2 ? 2 : 4 / nwx;
+}
+
+// A small batch: fewer row blocks than 4/3 of the workgroups that run at once.
+static bool small_batch(const rsst_config* c, int nbox, const int strip[4]) {
+  long long blocks = 0;
+  for (int b = 0; b < nbox; ++b) {
+    const int nwx = (c[b].n[0] + 63) / 64, rows = chunks_of(c[b], false) * std::min(strip[nwx - 1], c[b].n[1]);
+    blocks += (c[b].n[1] + rows - 1) / rows;
+  }
+  return blocks < 4 * 256 * kBatchPerCU / 3;
+}
+
+// Row blocks of one box and their dependency lists, appended to `items`.  A
+// block is `groups` chunks of `km` rows, marched along y.
+static int plan_box(const rsst_config& c, const int strip[4], bool halve, int b, std::vector<Item>& items, int& km,
                     int& groups, int& nblk) {
   const int nx = c.n[0], nm = c.n[1];
   const int nwx = (nx + 63) / 64;
-  groups = 4 / nwx;
+  groups = chunks_of(c, halve);
   km = strip[nwx - 1] < nm ? strip[nwx - 1] : nm;
   const int nchunk = (nm + km - 1) / km;
   nblk = (nchunk + groups - 1) / groups;
@@ -494,6 +515,7 @@ static int batch_build(rsst_batch_s* h, void* U) {
   std::vector<int> order;
   int qfirst[kXcds + 1];
   h->local = deal_boxes(h->cfg, order, qfirst);
+  const bool halve = small_batch(h->cfg.data(), h->nbox, h->strip);
   int qu = 0;
   for (int o = 0; o < h->nbox; ++o) {
     const int b = order[o];
@@ -502,7 +524,7 @@ static int batch_build(rsst_batch_s* h, void* U) {
     BoxDev& B = h->boxes[b];
     B.rbase = (int)h->items.size();
     int km = 0, groups = 0, nblk = 0;
-    const int ps = plan_box(c, h->strip, b, h->items, km, groups, nblk);
+    const int ps = plan_box(c, h->strip, halve, b, h->items, km, groups, nblk);
     if (ps != RSST_OK) return ps;
     StageArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -661,7 +683,7 @@ int rsst_batch_init(const rsst_config* boxes, int nbox, const int64_t* offsets, 
   // size item tables for the shortest strips the tile setter accepts (8 rows)
   long long cap_items = 0;
   for (int b = 0; b < nbox; ++b) {
-    const int nwx = (boxes[b].n[0] + 63) / 64, groups = 4 / nwx;
+    const int groups = chunks_of(boxes[b], true);
     cap_items += ((boxes[b].n[1] + 7) / 8 + groups - 1) / groups;
   }
   const size_t es = h->prec == RSST_FP32_PERT ? 4 : 8;
@@ -703,9 +725,10 @@ int rsst_batch_plan(const rsst_config* boxes, int nbox, const int strip_rows[4],
   for (int c = 0; c < 4; ++c)
     if (strip_rows[c] < 8 || strip_rows[c] > 256) return RSST_E_ARG;
   std::vector<Item> items;
+  const bool halve = small_batch(boxes, nbox, strip_rows);
   for (int b = 0; b < nbox; ++b) {
     int km = 0, groups = 0, nblk = 0;
-    const int ps = plan_box(boxes[b], strip_rows, b, items, km, groups, nblk);
+    const int ps = plan_box(boxes[b], strip_rows, halve, b, items, km, groups, nblk);
     if (ps != RSST_OK) return ps;
     for (size_t i = items.size() - nblk; i < items.size(); ++i) {
       const Item& it = items[i];
