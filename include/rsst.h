@@ -349,6 +349,11 @@ int rsst_batch_get_tiles(rsst_batch h, int strip_rows[4]);
 int rsst_batch_plan(const rsst_config* boxes, int nbox, const int strip_rows[4], int* table, int cap,
                     int* nitem);
 
+/* The queues a run of these boxes takes its items from (on the host only, no
+ * device call): 8, one per XCD, each holding whole boxes, where their work deals
+ * out evenly enough, else 1. */
+int rsst_batch_queues(const rsst_config* boxes, int nbox, int* nqueue);
+
 /* nsteps SSP-RK2 steps of every box of U_all, in place, enqueued on stream.
  * 1 <= nsteps <= max_steps.  The first call (or a call with a different
  * U_all, nsteps or strip rows) synchronises the stream, uploads the tables

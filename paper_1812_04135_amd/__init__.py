@@ -100,7 +100,7 @@ def lib():
                      "rsst_batch_get_tiles", "rsst_batch_run", "rsst_batch_times", "rsst_batch_poll",
                      "rsst_batch_destroy", "rsst_batch_plan", "rsst_adjoint_step", "rsst_adjoint_step_u1",
                      "rsst_step_out", "rsst_adjoint_run", "rsst_steps_out", "rsst_workspace_bytes", "rsst_init_in",
-                     "rsst_plan"):
+                     "rsst_plan", "rsst_batch_queues"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -405,6 +405,14 @@ def rsst_batch_plan(cfgs, strip_rows=(16, 16, 16, 16)) -> np.ndarray:
     _check(lib().rsst_batch_plan(arr, len(cs), sr, tab.ctypes.data_as(ctypes.POINTER(ctypes.c_int)),
                                  n.value, ctypes.byref(n)), "rsst_batch_plan")
     return tab
+
+
+def rsst_batch_queues(cfgs) -> int:
+    """Queues of a batch of these boxes (host only): 8, one per XCD, or 1."""
+    cs = [c if isinstance(c, rsst_config) else make_config(c) for c in cfgs]
+    n = ctypes.c_int()
+    _check(lib().rsst_batch_queues((rsst_config * len(cs))(*cs), len(cs), ctypes.byref(n)), "rsst_batch_queues")
+    return n.value
 
 
 def rsst_batch_set_tiles(h, strip_rows):

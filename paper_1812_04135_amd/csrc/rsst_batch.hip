@@ -747,6 +747,17 @@ int rsst_batch_plan(const rsst_config* boxes, int nbox, const int strip_rows[4],
   return RSST_OK;
 }
 
+int rsst_batch_queues(const rsst_config* boxes, int nbox, int* nqueue) {
+  if (!boxes || nbox < 1 || !nqueue) return RSST_E_ARG;
+  const std::vector<int64_t> off(nbox, 0);
+  const int st = batch_validate(boxes, nbox, off.data());
+  if (st != RSST_OK) return st;
+  std::vector<int> order;
+  int qfirst[kXcds + 1];
+  *nqueue = deal_boxes(std::vector<rsst_config>(boxes, boxes + nbox), order, qfirst) ? kXcds : 1;
+  return RSST_OK;
+}
+
 int rsst_batch_set_tiles(rsst_batch h, const int strip_rows[4]) {
   if (!h || !strip_rows) return RSST_E_ARG;
   for (int c = 0; c < 4; ++c)
