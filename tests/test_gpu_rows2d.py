@@ -20,7 +20,7 @@ CASES = [([61, 40], True, 1), ([64, 4101], True, 0), ([63, 5002], True, 1),
          ([128, 33], False, 1), ([125, 1024], True, 1), ([122, 2203], False, 1),
          ([256, 97], False, 1), ([245, 512], True, 1), ([241, 3001], False, 1),
          ([512, 34], True, 1), ([490, 129], False, 1), ([384, 256], False, 1), ([190, 10923], False, 1),
-         ([384, 257], True, 0), ([256, 1100], False, 0), ([512, 520], False, 0), ([70, 61], True, 0)]
+         ([1000, 1030], False, 0), ([384, 257], True, 0), ([256, 1100], False, 0), ([512, 520], False, 0), ([70, 61], True, 0)]
 
 
 def _case(n, walls, seed=0):
@@ -62,9 +62,11 @@ def test_steps_agree_over_chunks_and_match_oracle(n, walls, rows, monkeypatch):
         assert ref[3] == 0
         if p["step"]:
             assert _same(_run(cfg, U, 3, "steps", **kw), ref)
-        for km in ("1", "2", "7", str(p["chunk"] + 1)):
+        for km in ("1", "2", "7", str(p["chunk"] + 1), "4096"):
             monkeypatch.setenv("RSST_KM", km)
             assert _same(_run(cfg, U, 3, **kw), ref), km
+            if km != "4096":  # a pair of one-launch steps, where the grid has them, and a single one
+                assert _same(_run(cfg, U, 3, "steps", **kw), ref), km
         monkeypatch.delenv("RSST_KM")
         if not kw and n[0] * n[1] <= 1 << 20:
             Uo, to, _ = oracle.run(cfg, U0, 3)
