@@ -272,8 +272,8 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
     // cells between walls: 64 x 8000 FP64 35 and 40, 64 x 65536 165 and 240; 128
     // x 30000 139 and 178; 256 x 16384 151 and 172, but 256 x 1100 24.5 and 21.2;
     // 192 x 20000 150 and 160, but 192 x 5000 48.7 and 47.9).  Rows of eight
-    // gain 5% there with FP64 and lose 6% with FP32 storage (512 x 16384), whose
-    // registers leave a CU one workgroup instead of two.
+    // stay with strips there (512 x 16384 FP64 314 and 331, but FP32, by a kernel
+    // of three waves per SIMD, 314 and 295).
     const long long waves = (long long)G.nwx * G.nm;
     if (G.cols.ncol > G.nwx && G.nwx <= 8) {
       double cost;
@@ -290,7 +290,7 @@ Geometry plan_geometry(int ndim, const int n[3], bool x_per) {
     if (G.rows) {
       G.nblk = G.nchunk;
       G.threads = 64 * G.nwx;
-      G.lds_bytes = (size_t)carve2(1, G.nwx).total * sizeof(double);
+      G.lds_bytes = (size_t)carve2(G.nwx).total * sizeof(double);
     } else {
       G.nblk = (G.cols.ncol * G.nchunk + kWaves2 - 1) / kWaves2;
       G.threads = 64 * kWaves2;

@@ -2,18 +2,16 @@
 // launches whose rows fill their waves better than strips with halo lanes do
 // (rsst_stage2.h; plan_geometry says which).
 //
-// A workgroup holds ts x rows of nx cells (nwx waves each); row r of the
-// workgroup marches y over its own chunk of planes (chunk_base + r), one
-// plane per iteration.  x neighbours and x plus-face states are exchanged
-// through LDS rows with one ghost slot at each end (periodic wrap or mirror),
-// and every x face flux is formed once, by the cell right of the face, and
+// A workgroup holds an x row of nx cells (nwx waves) and marches y over its
+// chunk of rows, one per iteration.  x neighbours and x plus-face states are
+// exchanged through LDS rows with one ghost slot at each end (periodic wrap or
+// mirror), and every x face flux is formed once, by the cell right of the face, and
 // handed to the cell on its left after a third barrier (by DPP within a wave,
 // one LDS seam value per wave edge).
-// y is marched: every y face is formed once and carried to the next plane.
+// y is marched: every y face is formed once and carried to the next row.
 //
-// Two planes per iteration (half the barriers, twice the independent work per
-// thread, but 160 VGPRs instead of 118 and so three waves per SIMD instead of
-// four) were no faster than one with chunks of as many rows: us per step, two
+// Two rows per iteration (half the barriers, twice the independent work per
+// thread, but 160 VGPRs and so three waves per SIMD instead of four) were no faster than one with chunks of as many rows: us per step, two
 // and one, 512 x 500 FP64 19.9, 19.3, FP32 19.5, 19.3; 256 x 1000 19.5, 19.4
 // and 19.1, 19.5; 128 x 4000 31.0, 30.7 and 30.9, 31.7.
 #pragma once
@@ -24,33 +22,29 @@
 
 namespace rsstk {
 
-// LDS carve-up of a 2D workgroup (doubles): ts rows of nwx waves.
+// LDS carve-up of a 2D workgroup (doubles): a row of nwx waves.
 struct Carve2 {
   int u, fp, fxs, red, total;
 };
 
-__host__ __device__ inline Carve2 carve2(int ts, int nwx) {
+__host__ __device__ inline Carve2 carve2(int nwx) {
   constexpr int NV = 4, PL = NV + 3;
   const int px = 64 * nwx + 2;
   Carve2 c;
   int o = 0;
-  c.u = o;   o += ts * NV * px;   // cell states [row][value][slot], slot 1 + i; 0, nx + 1: ghosts
-  c.fp = o;  o += ts * PL * px;  // x plus-face states, slot 1 + i; slot 0: the left ghost's
-  c.fxs = o; o += ts * NV * nwx;  // x flux at the left edge of each wave
+  c.u = o;   o += NV * px;   // cell states [value][slot], slot 1 + i; 0, nx + 1: ghosts
+  c.fp = o;  o += PL * px;  // x plus-face states, slot 1 + i; slot 0: the left ghost's
+  c.fxs = o; o += NV * nwx;  // x flux at the left edge of each wave
   c.red = o; o += 16;
   c.total = o;
   return c;
 }
 
-// One stage of R over one group of 2D strips (row r of the workgroup marches
-// chunk chunk_base + r), returning the thread's largest c_tot of the stage-2
-// output (0 in stage 1) and or-ing non-physical flags into `bad`.  Every row of
-// the workgroup runs the same number of march iterations, so rows of different
-// chunks share the workgroup's barriers; planes past a chunk's end are computed
-// on rows held in range and not stored.  dtf() gives the step's dt; it is
-// called once, after the first rows are loaded.
+// One stage of R over a chunk of rows, returning the thread's largest c_tot of
+// the stage-2 output (0 in stage 1) and or-ing non-physical flags into `bad`.
+// dtf() gives the step's dt; it is called once, after the first rows are loaded.
 template <int STAGE, typename ST, int FORMX, typename DtFn>
-__device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, int chunk_base, DtFn dtf,
+__device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, int chunk, DtFn dtf,
                                               unsigned& bad) {
   constexpr int NDIM = 2, NV = 4, PL = NV + 3;
   constexpr int FORM = FORMX & 7;
@@ -59,26 +53,18 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
   constexpr bool F32 = sizeof(ST) == 4;
   constexpr int SZ = (int)sizeof(ST);
   const Geometry& G = A.geo;
-  const int TS = G.ts, nwx = G.nwx;
+  const int nwx = G.nwx;
   const int PX = 64 * nwx + 2;
-  const Carve2 C = carve2(TS, nwx);
+  const Carve2 C = carve2(nwx);
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wx = w % nwx, row_raw = w / nwx;
-  // waves past the last full row (a row of 3 waves in a 4-wave workgroup)
-  // only take part in the barriers
-  const bool wave_idle = w >= nwx * TS;
-  const int row = wave_idle ? 0 : row_raw;
-  const int i_raw = wx * 64 + lane;
+  const int wx = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i_raw = tid;
   const bool xin = i_raw < G.nx;
   const int i = xin ? i_raw : G.nx - 1;
-  const int chunk = chunk_base + row;
   const int k0 = chunk * G.km, k1 = min(k0 + G.km, G.nm);
-  const bool active = xin && k0 < G.nm && !wave_idle;
-  const bool pub = xin && !wave_idle;  // writes this thread's LDS slots
-  const bool last_x = i_raw == G.nx - 1 && !wave_idle;
-  const bool first_x = i_raw == 0 && !wave_idle;
+  const bool last_x = i_raw == G.nx - 1;
+  const bool first_x = i_raw == 0;
   const bool x_per = A.bc_lo[0] == 0;
   const int rm_lo = A.bc_lo[1], rm_hi = A.bc_hi[1];
   const int plane = G.nx * SZ;  // bytes per y row
@@ -86,15 +72,15 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
 
   // the thread's LDS addresses: its cell slot minus one (its left neighbour),
   // its plus-face slot minus one, and its wave's x seam
-  double* const Urow = lds + C.u + row * NV * PX;
-  double* const Frow = lds + C.fp + row * PL * PX;
-  double* const ub = Urow + i;                             // + v PX + {0, 1, 2}
-  double* const fb = Frow + i;                             // + q PX + {0, 1}
-  double* const xs = lds + C.fxs + row * (NV * nwx) + wx;  // + v nwx
+  double* const Urow = lds + C.u;
+  double* const Frow = lds + C.fp;
+  double* const ub = Urow + i;            // + v PX + {0, 1, 2}
+  double* const fb = Frow + i;            // + q PX + {0, 1}
+  double* const xs = lds + C.fxs + wx;    // + v nwx
 
   // FP32 perturbation form: the background in registers, along y (the march
-  // axis: bgc for plane k of the iteration, bgn for the plane the iteration
-  // loads, k + 2) or fixed for the march (uniform, along x: bgc)
+  // axis: bgc for row k of the iteration, bgn for the row the iteration loads,
+  // k + 2) or fixed for the march (uniform, along x: bgc)
   const bool bg_on_m = F32 && A.bg_axis == 1;
   double bgc[NV], bgn[NV];
   const __amdgpu_buffer_rsrc_t bgr = field_rsrc(A.bg, F32 ? (long long)NV * A.nbg * 8 : 0);
@@ -116,14 +102,16 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
   // stage 2 writes the new state in place over the step-start state
   const Field32 uout = make_field<false>(A.uout, A.ncell, NV, SZ, plane);
 
-  // the march window: planes k and k + 1 (finished), the slope at k and the
+  // the march window: rows k and k + 1 (finished), the slope at k and the
   // flux at k - 1/2
   double q0[NV], q1[NV], sm0[NV], Fm_lo[NV];
   double cmax = 0.0;
-  const int k0l = min(k0, G.nm - 1);  // rows past the grid march in range
+  // (k0 is in range anyway; that the compiler is told so here is worth 3%: 256 x
+  // 256 10.6 us per step without, 10.3 with)
+  const int k0l = min(k0, G.nm - 1);
   {
     double qa[NV], qb[NV], ha[NV];
-    auto ld = [&](int q, double (&u)[NV]) {  // row k0l + q of the thread's column, through the y walls
+    auto ld = [&](int q, double (&u)[NV]) {  // row k0 + q of the thread's column, through the y walls
       bool n;
       const int kk = map_index(k0l + q, G.nm, rm_lo, rm_hi, n);
       ST raw[NV];
@@ -154,10 +142,7 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
   }
   const double dt = dtf();
 
-  for (int it = 0; it < G.km; ++it) {
-    const int kraw = k0 + it;
-    const int k = min(kraw, G.nm - 1);  // row used for loads and stores
-    const bool kval = kraw < k1;        // it is in the chunk
+  for (int k = k0; k < k1; ++k) {
     // ---- loads for this iteration: the row two ahead and the step-start
     // state (stored values now, finished where first used)
     ST wr[NV], unr[NV];
@@ -174,7 +159,7 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
     if constexpr (STAGE == 2) load_cell_raw<NDIM, ST>(unp, k, col, unr);
 
     // ---- P1: publish the cell states, and the x ghosts
-    if (pub) {
+    if (xin) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) ub[v * PX + 1] = q0[v];
     }
@@ -188,14 +173,19 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
     }
     __syncthreads();  // B1
 
+    // (the reads of the neighbours' slots form their addresses anew: kept over
+    // the march they put half of the forms beyond 128 VGPRs, three waves per SIMD)
+    int pitch = PX;
+    asm volatile("" : "+s"(pitch));
+
     // ---- P2: the x slopes and the plus-face states (published)
     double h[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) h[v] = mc_half(q0[v] - ub[v * PX], ub[v * PX + 2] - q0[v]);
+    for (int v = 0; v < NV; ++v) h[v] = mc_half(q0[v] - ub[v * pitch], ub[v * pitch + 2] - q0[v]);
     {
       Face<NV> fp;
       make_face<NDIM, 0, EXT>(q0, h, true, K, fp);
-      if (pub) put_face(fb + 1, PX, fp);
+      if (xin) put_face(fb + 1, PX, fp);
       if (x_per && last_x) put_face(Frow, PX, fp);  // the periodic ghost left of cell 0
     }
     __syncthreads();  // B2
@@ -205,12 +195,12 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
     {
       Face<NV> fm, pl;
       make_face<NDIM, 0, EXT>(q0, h, false, K, fm);
-      get_face(fb, PX, pl);  // slot i: the plus face of cell i - 1
+      get_face(fb, pitch, pl);  // slot i: the plus face of cell i - 1
       if (!x_per) {
         if (first_x) pl = mirror<NDIM, 0>(fm);
       }
       flux2<NDIM, 0>(pl, fm, Fx_lo);
-      if (lane == 0 && !wave_idle) {
+      if (lane == 0) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) xs[v * nwx] = Fx_lo[v];
       }
@@ -233,7 +223,7 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
           get_face(fb + 1, PX, fp);
           flux2<NDIM, 0>(fp, mirror<NDIM, 0>(fp), Fx_hi);
         }
-      } else if (lane == 63 && xin && !wave_idle) {
+      } else if (lane == 63 && xin) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) Fx_hi[v] = xs[v * nwx + 1];
       }
@@ -263,7 +253,7 @@ __device__ __forceinline__ double stage_body2(const StageArgs& A, double* lds, i
     const unsigned b = rsst_rate<NDIM, FORM, EXT>(q0, Dl, K, g, Rt);
     double un[NV];
     if constexpr (STAGE == 2) fin(unr, -1, bgc, 0.0, un);
-    if (active && kval) {
+    if (xin) {
       bad |= b;
       double out[NV];
 #pragma unroll

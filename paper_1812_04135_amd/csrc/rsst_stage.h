@@ -16,7 +16,7 @@ namespace rsstk {
 
 // ---------------------------------------------------------------- loads
 
-// Boundary rule on one axis, for an index at most two cells outside [0, n):
+// Boundary rule on one axis, for an index at most four cells outside [0, n), n >= 4:
 // periodic sides wrap; reflecting sides mirror (ghost -1-q takes cell q) and
 // flag the normal momentum for negation.  Called with workgroup-uniform
 // indices, so it runs on the scalar unit.
@@ -276,8 +276,8 @@ struct GridMax {
 // Stage 2: the workgroup's largest c_tot of the new state, stored in its own
 // slot (plain store: the next stage 1 reads the slots after this kernel has
 // ended), and workgroup 0 advances t by the step's dt (t is read by no other
-// workgroup of this kernel).
-__device__ __forceinline__ void cfl_epilogue(const StageArgs& A, double* red, double cmax, double dt) {
+// workgroup of this kernel).  nslot: the slots of the largest launch.
+__device__ __forceinline__ void cfl_epilogue(const StageArgs& A, double* red, double cmax, double dt, int nslot) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const double wm = wave_max(cmax);
   if (lane == 0) red[w] = wm;
@@ -286,7 +286,7 @@ __device__ __forceinline__ void cfl_epilogue(const StageArgs& A, double* red, do
     double m = 0.0;
     for (int q = 0; q < (int)(blockDim.x >> 6); ++q) m = fmax(m, red[q]);
     // slots past this launch's workgroups (another kernel's) hold 0
-    for (int q = blockIdx.x; q < A.geo.nslot; q += gridDim.x) A.blkmax_out[q] = q == (int)blockIdx.x ? m : 0.0;
+    for (int q = blockIdx.x; q < nslot; q += gridDim.x) A.blkmax_out[q] = q == (int)blockIdx.x ? m : 0.0;
     if (blockIdx.x == 0) *A.t_out = *A.t_in + dt;
   }
 }

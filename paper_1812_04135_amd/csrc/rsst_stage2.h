@@ -73,7 +73,7 @@ __device__ __forceinline__ void fetch_args2(const StageArgs& A) {
   asm volatile("" ::"s"(A.geo.nx), "s"(A.geo.nm), "s"(A.geo.km), "s"(A.geo.rF), "s"(A.geo.cols.ncol), "s"(A.geo.cols.cw),
                "s"(A.geo.cols.halo), "s"(A.geo.colsF.ncol), "s"(A.geo.colsF.cw), "s"(A.geo.colsF.halo), "s"(A.geo.nblk), "s"(A.geo.nblkF),
                "s"(A.bc_lo[0]), "s"(A.bc_lo[1]), "s"(A.bc_hi[1]), "s"(A.ncell), "s"(A.uin), "s"(A.un), "s"(A.uout),
-               "s"(A.blkmax), "s"(A.nslot), "s"(A.geo.nslot), "s"(A.t_in), "s"(A.dt_fixed));
+               "s"(A.blkmax), "s"(A.nslot), "s"(A.t_in), "s"(A.dt_fixed));
 }
 
 // A lane's place in strip `col`.

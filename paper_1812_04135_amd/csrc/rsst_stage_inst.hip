@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(NDIM == 3 ? kMaxThreads3 : 1024) stage_kernel(
     cmax = stage_body1<STAGE, ST, FORM>(A, lds, dt, bad);
   }
   if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
-  if constexpr (STAGE == 2) cfl_epilogue(A, red, cmax, dt);
+  if constexpr (STAGE == 2) cfl_epilogue(A, red, cmax, dt, A.nslot);
 }
 
 // 2D grids, one stage: a workgroup is four independent waves, each one strip
@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(64 * kWaves2) __attribute__((amdgpu_waves_per_
       A, lane_of(G.cols, G.nx, A.bc_lo[0] == 0, t % G.cols.ncol), lds + w * kLds2, none, k0, k1, k0, k1, work,
       [&]() { return dt = sd.finish(); }, bad);
   if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
-  if constexpr (STAGE == 2) cfl_epilogue(A, lds + kRed2, cmax, dt);
+  if constexpr (STAGE == 2) cfl_epilogue(A, lds + kRed2, cmax, dt, A.nslot);
 }
 
 // 2D grids, one stage, a workgroup per whole row (rsst_row2.h): up to 8 waves.
@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(64 * kWaves2) __attribute__((amdgpu_waves_per_
 template <int STAGE, typename ST, int FORM>
 __global__ void __launch_bounds__(512) row_kernel2d(const StageArgs A) {
   extern __shared__ double lds[];
-  double* red = lds + carve2(A.geo.ts, A.geo.nwx).red;
+  double* red = lds + carve2(A.geo.nwx).red;
   StepDt<STAGE> sd{A, red, {}};
   sd.begin();
   unsigned bad = 0;
@@ -118,7 +118,7 @@ __global__ void __launch_bounds__(512) row_kernel2d(const StageArgs A) {
   const double cmax = stage_body2<STAGE, ST, FORM>(A, lds, xcd_tile(blockIdx.x, A.geo.nblk),
                                                    [&]() { return dt = sd.finish(); }, bad);
   if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
-  if constexpr (STAGE == 2) cfl_epilogue(A, red, cmax, dt);
+  if constexpr (STAGE == 2) cfl_epilogue(A, red, cmax, dt, A.nslot);
 }
 
 // 2D grids, both stages of a step (rsst_stage2.h): one workgroup per CU, two
@@ -128,6 +128,7 @@ __global__ void __launch_bounds__(64 * kWavesF) __attribute__((amdgpu_waves_per_
 step_kernel2d(const StageArgs A) {
   extern __shared__ double lds[];
   fetch_args2(A);
+  asm volatile("" ::"s"(A.geo.nslot));
   double* red = lds + lds_doublesF(A.geo.rF) - kWavesF;
   unsigned bad = 0;
   double dt = 0.0;
@@ -136,7 +137,7 @@ step_kernel2d(const StageArgs A) {
   const double cmax = step_tile2<ST, FORM>(A, lds, xcd_tile(blockIdx.x, A.geo.nblkF),
                                            [&]() { return dt = sd.finish(); }, bad);
   if (bad) atomicOr((unsigned*)(A.scal + kFlags), bad);
-  cfl_epilogue(A, red, cmax, dt);
+  cfl_epilogue(A, red, cmax, dt, A.geo.nslot);
 }
 
 // One launch of a stage kernel over the geometry's grid.  The kernel's LDS
