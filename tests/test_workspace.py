@@ -2,6 +2,7 @@
 freed with the solver, a caller's stays the caller's, and the rollout's is
 torch's."""
 import ctypes
+import time
 
 import pytest
 
@@ -52,6 +53,16 @@ def _free():
     return torch.cuda.mem_get_info()[0]
 
 
+def _held(most=0):
+    """Bytes of live tensors, once they are at most `most` or five seconds have
+    passed: autograd's worker thread drops its references to a gradient a moment
+    after the caller has it, for which it has to wait for the interpreter lock."""
+    end = time.monotonic() + 5.0
+    while torch.cuda.memory_allocated() > most and time.monotonic() < end:
+        time.sleep(0.01)
+    return torch.cuda.memory_allocated()
+
+
 @pytest.mark.gpu
 def test_closing_a_solver_returns_its_memory():
     R.Solver(W.base_cfg(2, [64, 64], xi=3.0)).close()  # the library and its kernels are loaded
@@ -90,8 +101,8 @@ def test_solver_in_a_used_block_equals_its_own(n, adjoint):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("every", [1, 3])
-def test_rollout_keeps_nothing_from_torch(every):
+@pytest.mark.parametrize("every,graph", [(1, True), (3, False), (3, True)])
+def test_rollout_keeps_nothing_from_torch(every, graph):
     from paper_1812_04135_amd.rollout import rollout
 
     cfg, U0 = W.random_state(2, [256, 200], seed_k=1950, xi=4.0)
@@ -99,11 +110,13 @@ def test_rollout_keeps_nothing_from_torch(every):
     def gradient():
         U = torch.from_numpy(U0).cuda().requires_grad_(True)
         xi = torch.tensor(4.0, dtype=torch.float64, device="cuda", requires_grad=True)
-        out = rollout(U, xi, cfg, 12, 1e-4, every)
+        out = rollout(U, xi, cfg, 12, 1e-4, every, graph)
         return torch.autograd.grad(out, (U, xi), torch.ones_like(out))
 
     first = [g.cpu() for g in gradient()]
+    held = _held()
     before = _free()
     for _ in range(3):
         assert all(torch.equal(a, b.cpu()) for a, b in zip(first, gradient()))
+    assert _held(held) == held
     assert _free() >= before - 4_000_000
