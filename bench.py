@@ -116,14 +116,15 @@ def pert_err(Ug, pert, nv):
     return max(float(np.abs(Ug[v] - pert[v]).max() / sc[v]) for v in range(nv))
 
 
-def batch_roofline(version, prec, eff_gbs, cell_updates_s):
+def batch_roofline(version, prec, eff_gbs, cell_updates_s, strip_rows):
     """HBM view of a batched run: algorithmic bytes (5 x 4 values per
     cell-update) over the run time against the 8 TB/s peak, and the HBM bytes
-    the committed counters of this revision measured per cell-update."""
+    the committed counters of this revision measured per cell-update, if they
+    were taken with these strip rows (longer strips read less)."""
     out = {"bound": "hbm", "achieved": round(eff_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(eff_gbs / HBM_PEAK_GBS, 4), "traffic_GBs": None}
     t = profile_json("traffic_batch512.json", version)
-    if t:
+    if t and t["strip_rows"] == list(strip_rows):
         b = t["bytes_per_cell_update"]["float" if prec == "fp32_pert" else "double"]
         out["traffic_GBs"] = round(b * cell_updates_s / 1e9, 1)
         out["traffic_frac"] = round(b * cell_updates_s / 1e9 / HBM_PEAK_GBS, 4)
@@ -193,7 +194,7 @@ def bench_batch(R, W, np, torch, stream, args):
             "Gcell_updates_s": round(ncell * nst / (best * 1e-3) / 1e9, 4),
             "effective_GBs": round(5 * 4 * es * ncell * nst / (best * 1e-3) / 1e9, 1),
             "roofline": batch_roofline(R.rsst_version(), prec, 5 * 4 * es * ncell * nst / (best * 1e-3) / 1e9,
-                                       ncell * nst / (best * 1e-3)),
+                                       ncell * nst / (best * 1e-3), tiles),
             "strip_rows": tiles, "tiles_from_cache": cached,
             "err_vs_oracle": max(errs), "err_kind": "perturbation scale (1e-5)" if prec == "fp32_pert"
             else "natural scales (1e-12)",
