@@ -130,8 +130,9 @@ enum rsst_flag {
                             adjoint calls (FP64 only): on a 2D grid
                             nvar * ncell doubles and three per 16 x 16 tile,
                             else nvar * ncell * (2 ndim + 3) doubles and four
-                            per 256 cells (128 in 3D up to 131072 cells).  The adjoint calls of one handle
-                            share it: order them on one stream.               */
+                            per 256 cells (128 in 3D up to 131072 cells).  The
+                            adjoint calls of one handle share it: order them
+                            on one stream.                                    */
 };
 
 typedef struct rsst_solver* rsst_handle;
@@ -331,9 +332,11 @@ typedef struct rsst_batch_s* rsst_batch;
 int rsst_batch_init(const rsst_config* boxes, int nbox, const int64_t* offsets, int max_steps,
                     void* stream, rsst_batch* out);
 
-/* Rows per strip of the march for boxes whose rows span 1, 2, 3 and 4 waves
- * (nx in 1..64, 65..128, 129..192, 193..256); each in [8, 256].  Takes
- * effect at the next run (re-captures the graph).  Default 16. */
+/* Rows of a chunk, which one march along y takes, for boxes whose rows span 1,
+ * 2, 3 and 4 waves (nx in 1..64, 65..128, 129..192, 193..256); each in [8, 256].
+ * A work item is a block of 4, 2, 1 and 1 chunks; 2 also for 61 to 64 cells
+ * between walls while the batch has fewer than 1024 blocks.  Any choice gives the
+ * same bits.  Takes effect at the next run (re-captures the graph).  Default 16. */
 int rsst_batch_set_tiles(rsst_batch h, const int strip_rows[4]);
 int rsst_batch_get_tiles(rsst_batch h, int strip_rows[4]);
 

@@ -3,11 +3,11 @@
 // graph and replayed.
 //
 // Work items are (stage q, box b, row block p), q = 2 n + stage - 1 for
-// step n.  A row block is `rows` rows (y, the marched axis) of a box, a
-// quarter of them marched by each wave of a 256-thread workgroup.  The boxes
-// are dealt to queues; tickets of a queue are handed out in q-major order by
-// one atomic counter, and an item only waits on items of its own box, which
-// hold smaller tickets of the same queue:
+// step n.  A row block is `rows` rows (y, the marched axis) of a box: a few
+// chunks of the strip rows, whose strips of x the four waves of a 256-thread
+// workgroup march.  The boxes are dealt to queues; tickets of a queue are
+// handed out in q-major order by one atomic counter, and an item only waits on
+// items of its own box, which hold smaller tickets of the same queue:
 //   * the row blocks of its box at q-1 that hold a row within two cells
 //     of its own rows (through the boundary rule: a periodic y wraps the
 //     first block onto the last ones), or whose rows are within two cells
@@ -62,12 +62,12 @@ constexpr int kLdAgent = 16;        // load cache policy sc1: agent scope, past 
 struct BoxDev {
   StageArgs s1, s2;  // stage views of the box (pointers into U_all / U1_all)
   double cfl_h;      // cfl * h of the box
-  int nblk;          // strip blocks
+  int nblk;          // row blocks
   int rbase;         // index of the box's first item in a stage
   int rows;          // rows of a block
 };
 
-// A work item: strip block `blk` of box `box`, and the blocks of the same
+// A work item: row block `blk` of box `box`, and the blocks of the same
 // box whose rows its stencil reads or whose stencil reads its rows (the
 // order it needs against the previous stage).
 constexpr int kMaxDeps = 8;
@@ -476,7 +476,16 @@ static int plan_box(const rsst_config& c, const int strip[4], bool halve, int b,
 // wave-rows, rows times strips).  Returns 1 for a queue per XCD.  Where the
 // fullest queue holds more than 1.25 of the mean (few boxes, or a few large
 // ones), all go to queue 0 for the whole chip and 0 is returned: the chip then
-// waits for one XCD longer than the write-backs between XCDs would cost.
+// waits for one XCD longer than the write-backs between XCDs would cost.  us
+// per step with one queue and with one per XCD, by the fullest queue's share of
+// the mean: FP64, 1: 8 boxes of 256 x 256 76 and 66; 1.2: 20 of 256 x 1024 368
+// and 298; 1.28: 25 of 256 x 512 182 and 182; 1.33: 12 of 256 x 1024 188 and 178;
+// 1.41: 17 of them 297 and 286; 1.6 and 1.78: 10 and 9 of them 171 and 176, 160
+// and 173.  FP32, in the same order: 89 and 71, 262 and 277, 174 and 185, 185 and
+// 190, 232 and 266, 174 and 191, 165 and 187.  Boxes of 64 and 128 rows a side
+// gain a little at any share (25 of 64 x 64 46 and 42, 19 of 128 x 128 72 and 63),
+// those of 256 lose (10 of 256 x 256 82 and 85).  1.25 is about where large
+// boxes turn in FP64; in FP32 they turn a little below it, small boxes above.
 static int deal_boxes(const std::vector<rsst_config>& cfg, std::vector<int>& order, int qfirst[kXcds + 1]) {
   const int nbox = (int)cfg.size();
   std::vector<long long> work(nbox);

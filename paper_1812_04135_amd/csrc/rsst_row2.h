@@ -11,9 +11,10 @@
 // y is marched: every y face is formed once and carried to the next row.
 //
 // Two rows per iteration (half the barriers, twice the independent work per
-// thread, but 160 VGPRs and so three waves per SIMD instead of four) were no faster than one with chunks of as many rows: us per step, two
-// and one, 512 x 500 FP64 19.9, 19.3, FP32 19.5, 19.3; 256 x 1000 19.5, 19.4
-// and 19.1, 19.5; 128 x 4000 31.0, 30.7 and 30.9, 31.7.
+// thread, but 160 VGPRs and so three waves per SIMD instead of four) were no
+// faster than one with chunks of as many rows: us per step, two and one, 512 x
+// 500 FP64 19.9, 19.3, FP32 19.5, 19.3; 256 x 1000 19.5, 19.4 and 19.1, 19.5;
+// 128 x 4000 31.0, 30.7 and 30.9, 31.7.
 #pragma once
 
 #include "rsst_stage.h"
