@@ -47,10 +47,12 @@ def test_size_and_arguments_on_host():
     assert R.rsst_workspace_bytes(_cfg([64, 64])) >= 8 * 4 * 64 * 64
 
 
-def _free():
+def _outside():
+    """Device memory in use but for what torch has reserved, whose cache grows and
+    shrinks with the tensors of other tests."""
     torch.cuda.synchronize()
-    torch.cuda.empty_cache()
-    return torch.cuda.mem_get_info()[0]
+    free, total = torch.cuda.mem_get_info()
+    return total - free - torch.cuda.memory_reserved()
 
 
 def _held(most=0):
@@ -66,11 +68,11 @@ def _held(most=0):
 @pytest.mark.gpu
 def test_closing_a_solver_returns_its_memory():
     R.Solver(W.base_cfg(2, [64, 64], xi=3.0)).close()  # the library and its kernels are loaded
-    before = _free()
+    before = _outside()
     s = R.Solver(W.base_cfg(2, [1024, 1000], xi=3.0))  # 33 MB
-    assert _free() <= before - 32_000_000
+    assert _outside() >= before + 32_000_000
     s.close()
-    assert _free() >= before - 4_000_000
+    assert _outside() <= before + 4_000_000
 
 
 @pytest.mark.gpu
@@ -114,9 +116,8 @@ def test_rollout_keeps_nothing_from_torch(every, graph):
         return torch.autograd.grad(out, (U, xi), torch.ones_like(out))
 
     first = [g.cpu() for g in gradient()]
-    held = _held()
-    before = _free()
+    held, before = _held(), _outside()
     for _ in range(3):
         assert all(torch.equal(a, b.cpu()) for a, b in zip(first, gradient()))
-    assert _held(held) == held
-    assert _free() >= before - 4_000_000
+    assert _held(held) <= held
+    assert _outside() <= before + 4_000_000
